@@ -301,10 +301,7 @@ int take_ws(void* d_ws, uint64_t ws_bytes, uint64_t need, char** out, bool* owne
 // Minimum / maximum keys (order-preserving integers of the float bits) set to
 // the identities of atomicMin / atomicMax, by a kernel (graph-capturable).
 int range_keys_reset(int* keys, uint32_t F, hipStream_t s) {
-    int rc = to_status(launch_fill_u32(reinterpret_cast<uint32_t*>(keys), 0x7FFFFFFFu, F, s));
-    if (rc == GPZ_OK)
-        rc = to_status(launch_fill_u32(reinterpret_cast<uint32_t*>(keys) + F, 0x80000000u, F, s));
-    return rc;
+    return to_status(launch_reset_stats(nullptr, 0, keys, F, s));
 }
 
 // Field range from its keys: 0, 0 when no finite value was seen, a zero
@@ -565,12 +562,10 @@ int gpz_error_stats(const float* const* h_orig, const float* const* h_recon,
     unsigned long long* acc = reinterpret_cast<unsigned long long*>(ws);
     int* keys = reinterpret_cast<int*>(acc + 3 * F);
     double* sumsq = reinterpret_cast<double*>(acc + 2 * F);
-    rc = to_status(launch_fill_u32(reinterpret_cast<uint32_t*>(acc), 0u, 6ull * F, s));
-    if (rc == GPZ_OK) rc = range_keys_reset(keys, F, s);
+    rc = to_status(launch_reset_stats(reinterpret_cast<uint32_t*>(acc), 6 * F, keys, F, s));
     if (rc == GPZ_OK && n > 0)
         rc = to_status(launch_bound_check(h_orig, h_recon, d_perm, n, F, h_eb, acc, acc + F,
-                                          sumsq, s));
-    if (rc == GPZ_OK && n > 0) rc = to_status(launch_field_range(h_orig, n, F, keys, s));
+                                          sumsq, keys, s));
     std::vector<unsigned long long> h(4 * F);
     if (rc == GPZ_OK)
         rc = to_status(hipMemcpyAsync(h.data(), acc, 32ull * F, hipMemcpyDeviceToHost, s));
@@ -617,7 +612,7 @@ int gpz_bound_check(const float* const* h_orig, const float* const* h_recon,
     rc = to_status(launch_fill_u32(reinterpret_cast<uint32_t*>(acc), 0u, 4ull * F, s));
     if (rc == GPZ_OK && n > 0)
         rc = to_status(launch_bound_check(h_orig, h_recon, d_perm, n, F, h_eb, acc, acc + F,
-                                          nullptr, s));
+                                          nullptr, nullptr, s));
     std::vector<unsigned long long> h(2 * F);
     if (rc == GPZ_OK)
         rc = to_status(hipMemcpyAsync(h.data(), acc, 16ull * F, hipMemcpyDeviceToHost, s));

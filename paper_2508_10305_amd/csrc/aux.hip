@@ -110,6 +110,17 @@ __global__ __launch_bounds__(256) void copy_records_batch(const CopyArgs* jobs,
     }
 }
 
+// Accumulators of the reporting calls in one launch: nzero words of zeros,
+// and nkeys minimum then nkeys maximum range keys at their identities.
+__global__ __launch_bounds__(256) void reset_stats(uint32_t* zero, uint32_t nzero, int* keys,
+                                                   uint32_t nkeys) {
+    for (uint32_t i = threadIdx.x; i < nzero; i += 256) zero[i] = 0u;
+    for (uint32_t i = threadIdx.x; i < nkeys; i += 256) {
+        keys[i] = 0x7FFFFFFF;
+        keys[nkeys + i] = (int)0x80000000;
+    }
+}
+
 __global__ void fill_u32(uint32_t* p, uint32_t value, uint64_t count) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) p[i] = value;
@@ -124,116 +135,275 @@ struct BoundArgs {
     uint32_t F;
     unsigned long long* viol;
     unsigned long long* maxerr_bits;
-    double* sumsq;  // nullable: sum of squared differences per field
+    double* sumsq;  // STATS: sum of squared differences per field
+    int* keys;      // STATS: range keys of the originals, [0, F) minima, [F, 2F) maxima
 };
 
-constexpr uint32_t kCheckChunk = 1024;  // positions per workgroup step
+// Order-preserving map of float bits to signed integers (-0 < +0).
+__device__ __forceinline__ int order_key(float v) {
+    int i = __float_as_int(v);
+    return i ^ ((i >> 31) & 0x7FFFFFFF);
+}
+
+__device__ __forceinline__ double wave_sum_f64(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+__device__ __forceinline__ double wave_max_f64(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+    return v;
+}
+
+// 16 bytes at 4-byte alignment (the hardware takes unaligned vector loads).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        unsigned long long t = __shfl_xor(v, o);
-        v = t > v ? t : v;
-    }
-    return v;
-}
 
-// Error-bound verification.  A 256-lane workgroup takes chunks of 1024
-// positions (lane t: positions 4t..4t+3), reads the permutation once per
-// chunk for all fields, the reconstructed values contiguously and the
-// originals by gather -- block-local for GPZ permutations, so each chunk's
-// originals come from one 4 KB window per field.  A pair passes when its bits
-// match or |recon - orig| <= eb in double; a permutation entry >= n counts
-// as a violation and is not read.  Per-field counts and maxima gather in LDS
-// (one slot per wave) and leave with one atomic per field per workgroup.
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
+constexpr uint32_t kCheckChunk = 1024;  // positions per wave step
+constexpr int kCheckItems = kCheckChunk / 64;
+// Workgroups per CU: 128 registers let four waves share a SIMD, whose loads
+// (8 KB each) cover the memory's latency without a prefetch.  With one (two
+// more fields' registers) the kernel spills at this occupancy: 196 us.
+constexpr uint32_t kCheckGroups = 4;
 
-__global__ __launch_bounds__(256) void bound_check_kernel(BoundArgs a) {
-    __shared__ unsigned long long sv[4][kMaxFields], sm[4][kMaxFields];
-    __shared__ double ss[4][kMaxFields];
-    const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-    for (uint32_t i = threadIdx.x; i < 4 * kMaxFields; i += 256) {
-        (&sv[0][0])[i] = 0;
-        (&sm[0][0])[i] = 0;
-        (&ss[0][0])[i] = 0.0;
-    }
-    __syncthreads();
-    const uint64_t nchunks = (a.n + kCheckChunk - 1) / kCheckChunk;
-    for (uint64_t c = blockIdx.x; c < nchunks; c += gridDim.x) {
-        const uint64_t j0 = c * kCheckChunk + 4 * threadIdx.x;
-        uint32_t src[4];
-        bool in[4];
+// Values 256k + 4 lane + e of a chunk that starts at p (whole, or those whose
+// bit is set in `live`; the others are 0).
+__device__ __forceinline__ void check_load(const float* p, bool whole, uint32_t live, uint32_t lane,
+                                           float (&v)[kCheckItems]) {
+    if (whole) {
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            in[i] = j0 + i < a.n;
-            src[i] = in[i] ? (a.perm ? a.perm[j0 + i] : (uint32_t)(j0 + i)) : 0u;
+        for (int k = 0; k < kCheckItems / 4; k++) {
+            const f32x4u t = __builtin_nontemporal_load(
+                reinterpret_cast<const f32x4u*>(p + 256 * k + 4 * lane));
+            v[4 * k] = t.x;
+            v[4 * k + 1] = t.y;
+            v[4 * k + 2] = t.z;
+            v[4 * k + 3] = t.w;
         }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kCheckItems; j++) {
+            const uint32_t i = 256u * (j / 4) + 4u * lane + (j & 3u);
+            v[j] = (live >> j) & 1u ? p[i] : 0.0f;
+        }
+    }
+}
+
+// Error-bound verification, with STATS also the sum of squared errors and the
+// finite range of the originals.  Each wave takes chunks of 1024 positions.
+// A field's originals in the chunk's own window come in with 16-byte loads
+// and are gathered through LDS, because a GPZ permutation is block-local (an
+// entry outside the window is read from memory, one outside [0, n) counts as
+// a violation and is not read); the same registers give the originals'
+// range, so they are read once.  A pair passes when its bits match or |recon - orig|
+// <= eb in double.
+//
+// The bound is the read of both arrays (and of the permutation once for all
+// fields), so the per-value work is kept to five double operations: the
+// largest error, the finite range and the presence of a NaN are tested once
+// per lane and chunk (a lane's sum is NaN exactly when one of its differences
+// is), and only chunks that fail a test count pairs one by one or reduce
+// across the wave.  16M x 6 with a permutation (0.83 GB): 141 us, 5.9 TB/s;
+// the check that gathered the originals from memory took 274 us and the
+// separate range pass another 100.
+template <bool STATS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void bound_check_kernel(BoundArgs a) {
+    __shared__ float win[4][kCheckChunk];
+    __shared__ double sm[4][kMaxFields], ss[4][kMaxFields];
+    __shared__ unsigned long long sv[4][kMaxFields];
+    __shared__ int skn[4][kMaxFields], skx[4][kMaxFields];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    float* const mywin = win[w];
+    sm[w][lane] = 0.0;
+    ss[w][lane] = 0.0;
+    sv[w][lane] = 0;
+    skn[w][lane] = 0x7FFFFFFF;
+    skx[w][lane] = (int)0x80000000;
+    wave_lds_sync();
+    const uint64_t nchunks = (a.n + kCheckChunk - 1) / kCheckChunk;
+    for (uint64_t c = (uint64_t)blockIdx.x * 4 + w; c < nchunks; c += (uint64_t)gridDim.x * 4) {
+        const uint64_t c0 = c * kCheckChunk;
+        const uint64_t left = a.n - c0;
+        const bool whole = left >= kCheckChunk;
+        // (opaque: no 64-bit index per position is kept across the chunks)
+        uint32_t ln = lane;
+        asm volatile("" : "+v"(ln));
+        // position of each pair's original: its offset in the window, or
+        // (bit set in `far`) elsewhere
+        uint32_t src[kCheckItems];
+        uint32_t live = 0xFFFFu, far = 0u;
+        if (whole && a.perm) {
+#pragma unroll
+            for (int k = 0; k < kCheckItems / 4; k++) {
+                const u32x4u t =
+                    *reinterpret_cast<const u32x4u*>(a.perm + c0 + 256 * k + 4 * ln);
+                src[4 * k] = t.x - (uint32_t)c0;
+                src[4 * k + 1] = t.y - (uint32_t)c0;
+                src[4 * k + 2] = t.z - (uint32_t)c0;
+                src[4 * k + 3] = t.w - (uint32_t)c0;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kCheckItems; j++) {
+                const uint32_t i = 256u * (j / 4) + 4u * ln + (j & 3u);
+                src[j] = i;
+                if (i >= left) live &= ~(1u << j);
+                else if (a.perm) src[j] = a.perm[c0 + i] - (uint32_t)c0;
+            }
+        }
+        // (past 2^32 the 32-bit entries never name the chunk's own window)
+        const uint32_t inwin = a.perm && (c0 >> 32) ? 0u
+                               : whole ? kCheckChunk : (uint32_t)left;
+#pragma unroll
+        for (int j = 0; j < kCheckItems; j++)
+            if (src[j] >= inwin) far |= 1u << j;
+        far &= live;
+        const bool plain = !__any(far != 0u || live != 0xFFFFu);
         for (uint32_t f = 0; f < a.F; f++) {
-            const float* x = a.orig[f];
-            const float* y = a.recon[f];
+            // (opaque: the compiler would keep a lane mask per bit, and spill
+            // them, across the loop over fields)
+            asm volatile("" : "+v"(live), "+v"(far));
+            float xn[kCheckItems], x[kCheckItems], y[kCheckItems];
+            check_load(a.orig[f] + c0, whole, live, ln, xn);
+            check_load(a.recon[f] + c0, whole, live, ln, y);
+            if (a.perm) {
+#pragma unroll
+                for (int k = 0; k < kCheckItems / 4; k++)
+                    reinterpret_cast<float4*>(mywin)[64 * k + ln] =
+                        make_float4(xn[4 * k], xn[4 * k + 1], xn[4 * k + 2], xn[4 * k + 3]);
+            }
+            if (STATS) {
+                // finite range of the window: a lane whose plain minimum or
+                // maximum is NaN or infinite filters its values one by one
+                float mn = xn[0], mx = xn[0];
+#pragma unroll
+                for (int j = 1; j < kCheckItems; j++) {
+                    mn = __builtin_elementwise_minimum(mn, xn[j]);
+                    mx = __builtin_elementwise_maximum(mx, xn[j]);
+                }
+                int kn = order_key(mn), kx = order_key(mx);
+                if (!whole || __any(!__builtin_isfinite(mn) || !__builtin_isfinite(mx))) {
+                    kn = 0x7FFFFFFF;
+                    kx = (int)0x80000000;
+#pragma unroll
+                    for (int j = 0; j < kCheckItems; j++) {
+                        if (((live >> j) & 1u) && __builtin_isfinite(xn[j])) {
+                            kn = min(kn, order_key(xn[j]));
+                            kx = max(kx, order_key(xn[j]));
+                        }
+                    }
+                }
+                if (__any(kn < skn[w][f] || kx > skx[w][f])) {
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) {
+                        kn = min(kn, __shfl_xor(kn, o));
+                        kx = max(kx, __shfl_xor(kx, o));
+                    }
+                    if (lane == 0) {
+                        skn[w][f] = min(kn, skn[w][f]);
+                        skx[w][f] = max(kx, skx[w][f]);
+                    }
+                }
+            }
+            if (a.perm) {
+                wave_lds_sync();
+#pragma unroll
+                for (int j = 0; j < kCheckItems; j++) x[j] = mywin[src[j] & (kCheckChunk - 1u)];
+                wave_lds_sync();  // gathered before the next field's window replaces it
+            } else {
+#pragma unroll
+                for (int j = 0; j < kCheckItems; j++) x[j] = xn[j];
+            }
             const double eb = (double)a.eb[f];
-            float yr[4], xo[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                yr[i] = in[i] ? y[j0 + i] : 0.0f;
-                xo[i] = in[i] && src[i] < a.n ? x[src[i]] : 0.0f;
-            }
-            unsigned long long v = 0;
             double m = 0.0, q = 0.0;
+            bool exact = plain;
+            if (plain) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                if (!in[i]) continue;
-                if (src[i] >= a.n) {  // not a permutation of [0, n)
-                    v++;
-                    continue;
+                for (int j = 0; j < kCheckItems; j++) {
+                    const double d = __builtin_fabs((double)y[j] - (double)x[j]);
+                    m = fmax(m, d);
+                    q = __builtin_fma(d, d, q);
                 }
-                const double d = __builtin_fabs((double)yr[i] - (double)xo[i]);
-                if (!__builtin_isnan(d)) {
-                    if (d > m) m = d;
-                    q += d * d;
+                exact = !__any(!(m <= eb) || __builtin_isnan(q));
+            }
+            if (!exact) {
+                unsigned long long v = 0;
+                m = 0.0;
+                q = 0.0;
+#pragma unroll
+                for (int j = 0; j < kCheckItems; j++) {
+                    if (!((live >> j) & 1u)) continue;
+                    float xo = x[j];
+                    // (opaque: neither the differences above nor a 64-bit
+                    // address per position are kept for this path)
+                    uint32_t at = src[j] + (uint32_t)c0;
+                    asm volatile("" : "+v"(xo), "+v"(at));
+                    if ((far >> j) & 1u) {
+                        if (at >= a.n) {  // not a permutation of [0, n)
+                            v++;
+                            continue;
+                        }
+                        xo = a.orig[f][at];
+                    }
+                    const double d = __builtin_fabs((double)y[j] - (double)xo);
+                    if (!__builtin_isnan(d)) {
+                        m = fmax(m, d);
+                        q = __builtin_fma(d, d, q);
+                    }
+                    if (f2u(xo) != f2u(y[j]) && !(d <= eb)) v++;
                 }
-                if (f2u(xo[i]) != f2u(yr[i]) && !(d <= eb)) v++;
+                v = wave_sum_u64(v);
+                if (lane == 0) sv[w][f] += v;
             }
-            v = wave_sum_u64(v);
-            const unsigned long long mb =
-                wave_max_u64((unsigned long long)__double_as_longlong(m));
-            if (a.sumsq) q = wave_sum_f64(q);
-            if (lane == 0) {
-                sv[w][f] += v;
-                if (mb > sm[w][f]) sm[w][f] = mb;
-                ss[w][f] += q;
+            if (__any(m > sm[w][f])) {
+                m = wave_max_f64(m);
+                if (lane == 0) sm[w][f] = fmax(m, sm[w][f]);
             }
+            if (STATS) {
+                q = wave_sum_f64(q);
+                if (lane == 0) ss[w][f] += q;
+            }
+            wave_lds_sync();
         }
     }
     __syncthreads();
     for (uint32_t f = threadIdx.x; f < a.F; f += 256) {
-        unsigned long long tv = 0, tm = 0;
+        unsigned long long tv = 0;
+        double tm = 0.0, tq = 0.0;
+        int kn = 0x7FFFFFFF, kx = (int)0x80000000;
         for (int i = 0; i < 4; i++) {
             tv += sv[i][f];
-            tm = sm[i][f] > tm ? sm[i][f] : tm;
+            tm = fmax(tm, sm[i][f]);
+            tq += ss[i][f];
+            kn = min(kn, skn[i][f]);
+            kx = max(kx, skx[i][f]);
         }
         if (tv) atomicAdd(&a.viol[f], tv);
-        if (tm) atomicMax(&a.maxerr_bits[f], tm);
-        if (a.sumsq) {
-            const double tq = ss[0][f] + ss[1][f] + ss[2][f] + ss[3][f];
+        if (tm > 0.0) atomicMax(&a.maxerr_bits[f], (unsigned long long)__double_as_longlong(tm));
+        if (STATS) {
             if (tq != 0.0) atomicAdd(&a.sumsq[f], tq);
+            if (kn <= kx) {
+                atomicMin(&a.keys[f], kn);
+                atomicMax(&a.keys[a.F + f], kx);
+            }
         }
     }
 }
 
 // Structure statistics of a stream: outliers per field (coded blocks) and
-// raw blocks.  One lane per block: the record offset comes from the
-// superblock table plus the lengths before the block in its superblock; the
-// lane walks the record's array headers.  Malformed structure sets *err.
+// raw blocks.  One lane per block, one wave per superblock: the record offset
+// is the superblock's plus an exclusive scan of the lengths across the wave
+// (each lane summing the lengths before its own took as long as the walk);
+// the lane walks the record's array headers, one dependent read per field,
+// which is what bounds it.  Malformed structure sets *err.
 struct StatsArgs {
     const uint32_t* in;
     uint64_t in_words;
@@ -257,15 +427,22 @@ __global__ __launch_bounds__(256) void stream_stats_kernel(StatsArgs a) {
     uint64_t off = 0, pos = 0;
     uint32_t len = 0, nn = 0;
     const uint32_t* rec = a.in + a.prefix;
+    static_assert(kSuper == 64, "one wave per superblock");
+    len = live ? lt[b] : 0u;
+    uint64_t before = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t t = __shfl_up(before, o);
+        before += (threadIdx.x & 63u) >= (uint32_t)o ? t : 0ull;
+    }
+    before -= len;
     if (live) {
         // superblock entry checked before use, lengths summed in 64 bits (at
         // most 63 of them): no sum wraps, an accepted record lies inside the
         // record area
         const uint32_t sb = b / kSuper;
         const uint64_t sup_off = (uint64_t)sup[2 * sb] | ((uint64_t)sup[2 * sb + 1] << 32);
-        off = sup_off;
-        for (uint32_t k = sb * kSuper; k < b; k++) off += lt[k];
-        len = lt[b];
+        off = sup_off + before;
         nn = (uint32_t)((uint64_t)(b + 1) * a.B <= a.n ? a.B : a.n - (uint64_t)b * a.B);
         bad = len < 1 || sup_off > rec_total || off > rec_total || (uint64_t)len > rec_total - off;
         if (!bad) {
@@ -313,12 +490,6 @@ struct RangeArgs {
     uint64_t cpf;  // chunks per field: ceil((n / 4) / (U * 256))
     int* keys;     // order-preserving integer keys: [0, F) minima, [F, 2F) maxima
 };
-
-// Order-preserving map of float bits to signed integers (-0 < +0).
-__device__ __forceinline__ int order_key(float v) {
-    int i = __float_as_int(v);
-    return i ^ ((i >> 31) & 0x7FFFFFFF);
-}
 
 __device__ __forceinline__ void range_take(float v, int& mn, int& mx) {
     if (__builtin_isfinite(v)) {
@@ -499,6 +670,12 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStrea
     return hipGetLastError();
 }
 
+hipError_t launch_reset_stats(uint32_t* zero, uint32_t nzero, int* keys, uint32_t nkeys,
+                              hipStream_t s) {
+    hipLaunchKernelGGL(reset_stats, dim3(1), dim3(256), 0, s, zero, nzero, keys, nkeys);
+    return hipGetLastError();
+}
+
 hipError_t launch_stream_stats(const uint32_t* in, uint64_t in_words, uint64_t n, uint32_t F,
                                uint32_t B, unsigned long long* outliers, unsigned long long* raw,
                                uint32_t* err, hipStream_t s) {
@@ -521,7 +698,7 @@ hipError_t launch_stream_stats(const uint32_t* in, uint64_t in_words, uint64_t n
 hipError_t launch_bound_check(const float* const* orig, const float* const* recon,
                               const uint32_t* perm, uint64_t n, uint32_t F, const float* eb,
                               unsigned long long* viol, unsigned long long* maxerr_bits,
-                              double* sumsq, hipStream_t s) {
+                              double* sumsq, int* keys, hipStream_t s) {
     BoundArgs a{};
     for (uint32_t f = 0; f < F; f++) {
         a.orig[f] = orig[f];
@@ -534,10 +711,14 @@ hipError_t launch_bound_check(const float* const* orig, const float* const* reco
     a.viol = viol;
     a.maxerr_bits = maxerr_bits;
     a.sumsq = sumsq;
-    uint64_t groups = (n + kCheckChunk - 1) / kCheckChunk;
-    if (groups > 8192) groups = 8192;
-    if (groups == 0) groups = 1;
-    hipLaunchKernelGGL(bound_check_kernel, dim3((uint32_t)groups), dim3(256), 0, s, a);
+    a.keys = keys;
+    const uint64_t need = ((n + kCheckChunk - 1) / kCheckChunk + 3) / 4;
+    const uint64_t most = (uint64_t)kCheckGroups * device_cu_count();
+    const uint64_t groups = need < 1 ? 1 : (need < most ? need : most);
+    if (sumsq)
+        hipLaunchKernelGGL(bound_check_kernel<true>, dim3((uint32_t)groups), dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL(bound_check_kernel<false>, dim3((uint32_t)groups), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -279,10 +279,16 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s);
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStream_t s);
+// nzero words at `zero` cleared and the range keys (nkeys minima, nkeys
+// maxima) set to the identities of atomicMin / atomicMax, in one launch.
+hipError_t launch_reset_stats(uint32_t* zero, uint32_t nzero, int* keys, uint32_t nkeys,
+                              hipStream_t s);
+// sumsq and keys (sums of squares, range keys of the originals) together or
+// neither.
 hipError_t launch_bound_check(const float* const* orig, const float* const* recon,
                               const uint32_t* perm, uint64_t n, uint32_t F, const float* eb,
                               unsigned long long* viol, unsigned long long* maxerr_bits,
-                              double* sumsq, hipStream_t s);
+                              double* sumsq, int* keys, hipStream_t s);
 hipError_t launch_stream_stats(const uint32_t* in, uint64_t in_words, uint64_t n, uint32_t F,
                                uint32_t B, unsigned long long* outliers, unsigned long long* raw,
                                uint32_t* err, hipStream_t s);
