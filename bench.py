@@ -33,7 +33,8 @@ def log(*a):
 
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_encode_cosmology64M.md")
-ENCODER_SOURCES = ("paper_2508_10305_amd/csrc/encode.hip", "paper_2508_10305_amd/csrc/gpz_internal.h")
+ENCODER_SOURCES = ("paper_2508_10305_amd/csrc/encode.hip", "paper_2508_10305_amd/csrc/encode_block.h",
+                   "paper_2508_10305_amd/csrc/gpz_internal.h")
 
 
 def encoder_source_hash() -> str:

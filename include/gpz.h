@@ -44,8 +44,8 @@ typedef enum {
 
 /* Compression parameters.
  * block_size : particles per block B, power of two, 64..4096.  256..2048
- *              run one wave per block; the other sizes (and float64 fields)
- *              run the generic kernels, one 256-lane workgroup per block.
+ *              run one wave per block (float64 fields: 1024 only); the other
+ *              sizes run the generic kernels, one 256-lane workgroup per block.
  *              Default 1024 (32 threads x 32 points per block, Sec. 4.2).
  * seg_bits   : K, 0..5: each key axis is cut into 2^K power-of-two segments
  *              (segment size proportional to the block's range, Sec. 4.1).
@@ -132,8 +132,8 @@ int gpz_compress_async(const float *const *h_fields, uint64_t n, uint32_t nfield
  * (|y - x| < eb in double); otherwise it is quantized from the doubles with
  * 64-bit steps (double arithmetic, grid indices up to 2^53 - 1).  Non-finite
  * values are stored verbatim (64-bit patterns).  The stream carries
- * GPZ_STREAM_F64 and decodes with gpz_decompress_f64 only.  Runs the generic
- * kernels; GPZ_FLAG_SINGLE_PASS gives GPZ_EUNSUPPORTED.  Sizes:
+ * GPZ_STREAM_F64 and decodes with gpz_decompress_f64 only.
+ * GPZ_FLAG_SINGLE_PASS gives GPZ_EUNSUPPORTED.  Sizes:
  * gpz_max_compressed_bytes_f64, gpz_compress_workspace_bytes_f64. */
 int gpz_compress_f64(const double *const *h_fields, uint64_t n, uint32_t nfields,
                      const float *h_eb, const gpz_params *p, void *d_out, uint64_t out_capacity,

@@ -138,8 +138,8 @@ bool alloc_fault();
 // Shared body of the compress entry points (float32 or float64 fields).
 // The wave-per-block encoder takes float32 snapshots at block sizes
 // 256..2048 and leaves blocks that need 64-bit grid steps to the generic
-// encoder; float64 fields and other block sizes go to the generic encoder
-// whole.
+// encoder; float64 snapshots have one of their own at the default block size
+// (8M x 6: 128 us against 389); the rest goes to the generic encoder whole.
 int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F, const float* h_eb,
                   const gpz_params* pp, void* d_out, uint64_t cap, uint64_t* h_out_bytes,
                   uint64_t* d_out_bytes, uint32_t* d_perm, void* d_ws, uint64_t ws_bytes,
@@ -214,8 +214,10 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
                : launch_fill_u32(w.ticket, 0u, w.clear_words - 2 * nb, s));
     tm.end();
     tm.begin(kEncode);
-    if (rc == GPZ_OK) rc = to_status(generic ? launch_encode_generic(ea, false, s)
-                                             : launch_encode(ea, single, s));
+    if (rc == GPZ_OK)
+        rc = to_status(f64 && B == 1024 ? launch_encode64(ea, s)
+                       : generic        ? launch_encode_generic(ea, false, s)
+                                        : launch_encode(ea, single, s));
     tm.end();
     if (!single) {
         ScanArgs sa{};

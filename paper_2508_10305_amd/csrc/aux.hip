@@ -169,8 +169,8 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 constexpr uint32_t kCheckChunk = 1024;  // positions per wave step
 constexpr int kCheckItems = kCheckChunk / 64;
 // Workgroups per CU: 128 registers let four waves share a SIMD, whose loads
-// (8 KB each) cover the memory's latency without a prefetch.  With one (two
-// more fields' registers) the kernel spills at this occupancy: 196 us.
+// (8 KB each) cover the memory's latency without a prefetch (with one, which
+// spilled at this occupancy, a whole 16M x 6 report took 295 us; 238 without).
 constexpr uint32_t kCheckGroups = 4;
 
 // Values 256k + 4 lane + e of a chunk that starts at p (whole, or those whose

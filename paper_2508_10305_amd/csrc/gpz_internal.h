@@ -275,6 +275,8 @@ __device__ __forceinline__ void scan_superblocks(const ScanArgs& a, uint64_t* pa
 // single_pass: one launch that also places the records (look-back);
 // otherwise records and lengths for launch_scan / launch_copy.
 hipError_t launch_encode(const EncodeArgs& a, bool single_pass, hipStream_t s);
+// float64 fields at block size 1024 (records and lengths, as launch_encode).
+hipError_t launch_encode64(const EncodeArgs& a, hipStream_t s);
 hipError_t launch_scan(const ScanArgs& a, hipStream_t s);
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s);
