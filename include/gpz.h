@@ -352,7 +352,8 @@ int gpz_batch_destroy(gpz_batch *b);
  * an event pair around each of its kernels.  gpz_timing_collect waits for
  * the recorded events, adds up the durations per kernel kind into
  * total_ms[kind] with launch counts[kind] (kind 0 encode, 1 workspace
- * clearing, 2 decode, 3 length scan, 4 record copy, 5 the generic kernels;
+ * clearing, 2 decode, 3 length scan, 4 record copy, 5 the generic kernels and
+ * the float64 decoder;
  * arrays of nkinds entries) and clears the log. */
 int gpz_set_timing(int enable);
 int gpz_timing_collect(double *total_ms, uint32_t *counts, int nkinds);

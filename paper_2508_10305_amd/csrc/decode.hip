@@ -11,98 +11,10 @@
 // between its lanes is ordered by wave_lds_sync().  Every read of the record
 // is checked against its length first; a malformed record sets the error
 // flag and the block is skipped.
-#include "generic_block.h"
+#include "decode_block.h"
 
 namespace gpz {
 namespace {
-
-template <int ITEMS>
-__device__ __forceinline__ uint32_t pad_addr(uint32_t p) {
-    return p + 4 * (p / ITEMS);
-}
-
-__device__ __forceinline__ bool eb_ok(float eb) {
-    return __builtin_isfinite(eb) && eb >= 0x1p-120f && eb <= 0x1p120f;
-}
-
-// Copy `count` words (at most 64*L) from global memory into LDS with
-// coalesced loads, all issued before the first LDS store, so the copy costs
-// one memory round trip.  The number of 64-word steps selects a fully
-// unrolled copy (a wave-uniform choice); inside the last step the lanes past
-// the end load the array's last word again (so every load stays in bounds)
-// and store it past the end, where the buffer still has room.  Offsets are
-// 32-bit byte offsets from the array start, so each load takes the array's
-// scalar base address and one offset register.
-template <int N>
-__device__ __forceinline__ void stage_steps(uint32_t* __restrict__ dst,
-                                            const uint32_t* __restrict__ src, uint32_t count,
-                                            uint32_t ln) {
-    const uint8_t* b = reinterpret_cast<const uint8_t*>(src);
-    uint32_t t[N];
-#pragma unroll
-    for (int u = 0; u < N; u++)
-        t[u] = *reinterpret_cast<const uint32_t*>(b + 4u * min(ln + 64u * u, count - 1));
-#pragma unroll
-    for (int u = 0; u < N; u++) dst[ln + 64u * u] = t[u];
-}
-
-template <int N>
-__device__ __forceinline__ void stage_pick(uint32_t steps, uint32_t* __restrict__ dst,
-                                           const uint32_t* __restrict__ src, uint32_t count,
-                                           uint32_t ln) {
-    if constexpr (N > 0) {
-        if (steps == N) stage_steps<N>(dst, src, count, ln);
-        else stage_pick<N - 1>(steps, dst, src, count, ln);
-    }
-}
-
-template <int L>
-__device__ __forceinline__ void stage_words(uint32_t* __restrict__ dst,
-                                            const uint32_t* __restrict__ src, uint32_t count,
-                                            uint32_t lane) {
-    if (count == 0) return;
-    stage_pick<L>((count + 63) / 64, dst, src, count, lane);
-}
-
-// Value i of a fixed-length array of width w held in LDS (bits [i*w, i*w+w)).
-__device__ __forceinline__ uint32_t extract(const uint32_t* __restrict__ words, uint32_t i,
-                                            uint32_t w, uint32_t mask) {
-    uint32_t bit = i * w;
-    uint32_t wd = bit >> 5;
-    uint32_t lo = words[wd], hi = words[wd + 1];
-    return __builtin_amdgcn_alignbit(hi, lo, bit & 31u) & mask;
-}
-
-__device__ __forceinline__ uint32_t low_mask(uint32_t w) { return w >= 32u ? ~0u : ((1u << w) - 1u); }
-
-// Sum over the wave of one 64-bit value per lane (every lane gets it).
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// Whether the stream's header or eb table does not describe the stream the
-// caller asked for (lane k < 8 checks header word k, every lane a share of
-// the eb table).  Per-lane result.
-__device__ __forceinline__ bool header_bad(const DecodeArgs& a, uint32_t lane) {
-    bool bad = false;
-    const uint32_t* ebt = a.in + kHeaderWords + 2 * nsuper_of(a.nblocks);
-    for (uint32_t f = lane; f < a.F; f += 64)
-        if (!eb_ok(u2f(ebt[f]))) bad = true;
-    if (lane < kHeaderWords) {
-        const uint32_t expect[kHeaderWords] = {kMagic, kVersion, (uint32_t)(a.n & 0xFFFFFFFFu),
-                                               (uint32_t)(a.n >> 32), a.F, a.B,
-                                               a.K | (a.KF << 8), a.nblocks};
-        uint32_t want = expect[0];
-#pragma unroll
-        for (uint32_t k = 1; k < kHeaderWords; k++) want = lane == k ? expect[k] : want;
-        // word 1 may carry the wide-record flag (a float32 stream otherwise)
-        const uint32_t got = lane == 1 ? (a.in[lane] & ~(2u << 16)) : a.in[lane];
-        if (got != want) bad = true;
-    }
-    return bad;
-}
 
 template <int ITEMS>
 struct DecodeSmem {
@@ -146,42 +58,10 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
     const uint64_t base = (uint64_t)b * B;
     const uint32_t nb = (uint32_t)((a.n - base) < B ? (a.n - base) : B);
     const uint32_t F = a.F, K = a.K, KF = a.KF;
-    const uint64_t nsup = nsuper_of(a.nblocks);
-    const uint32_t* sup = a.in + kHeaderWords;
-    const uint32_t* ebt = sup + 2 * nsup;
-    const uint32_t* lens = ebt + F;
-    const uint32_t* recs = a.in + a.prefix;
-    const uint64_t rec_total = a.in_words - a.prefix;
-
-    // ---- locate the record: superblock offset + lengths before it.  The
-    // superblock entry is checked against the record area before anything is
-    // added to it, and the lengths are summed in 64 bits, so no sum can wrap
-    // and every accepted [off, off + len) lies inside the record area.
-    const uint32_t sb = b / kSuper;
-    const uint32_t first = sb * kSuper;
-    const uint64_t sup_off = (uint64_t)sup[2 * sb] | ((uint64_t)sup[2 * sb + 1] << 32);
-    const uint64_t mine = (first + lane < b) ? (uint64_t)lens[first + lane] : 0ull;
-    const uint64_t sum = sup_off + wave_sum_u64(mine);
-    // every lane holds the same sum: taken from lane 0 it is a scalar, and so
-    // are the record pointer and every header word read through it
-    const uint64_t off = ((uint64_t)readlane((uint32_t)(sum >> 32), 0) << 32) |
-                         (uint64_t)readlane((uint32_t)sum, 0);
-    const uint32_t len = lens[b];
-    bool bad = sup_off > rec_total || off > rec_total || (uint64_t)len > rec_total - off;
-    if (b == 0 && (sup[0] | sup[1]) != 0u) bad = true;
-    if (a.exact && b + 1 == a.nblocks && off + len != rec_total) bad = true;
-    if (header_bad(a, lane)) bad = true;
-    if (b == first && sb > 0) {
-        // consistency of this superblock's offset with the previous one
-        const uint64_t pl = lens[first - kSuper + lane];
-        const uint64_t prev = ((uint64_t)sup[2 * sb - 2] | ((uint64_t)sup[2 * sb - 1] << 32));
-        if (prev > rec_total || prev + wave_sum_u64(pl) != off) bad = true;
-    }
-    if (__any(bad)) {
-        if (lane == 0) *a.err = 1u;
-        return;
-    }
-    const uint32_t* rec = recs + off;
+    const uint32_t* ebt = a.in + kHeaderWords + 2 * nsuper_of(a.nblocks);
+    const uint32_t* rec;
+    uint32_t len;
+    if (!locate_record(a, b, lane, 0u, rec, len)) return;
     const uint32_t h0 = len ? rec[0] : 0u;
     const uint32_t mode = h0 & 3u;
 
@@ -218,7 +98,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
     const uint32_t h1 = len > 1 ? rec[1] : 0xFFFFFFFFu;
     const uint32_t w_gap = h1 & 31u, w_cnt = (h1 >> 5) & 31u;
     const uint32_t s0 = (h1 >> 10) & 31u, s1 = (h1 >> 15) & 31u, s2 = (h1 >> 20) & 31u;
-    bad = len < 2 || (h1 >> 25) != 0u || U < 1 || U > nb || w_gap > 15 || w_cnt > 12;
+    bool bad = len < 2 || (h1 >> 25) != 0u || U < 1 || U > nb || w_gap > 15 || w_cnt > 12;
     bad |= (KF < 2 && s1 != 0) || (KF < 3 && s2 != 0);
     bad |= (s0 + K > 24) || (KF > 1 && s1 + K > 24) || (KF > 2 && s2 + K > 24);
     const uint32_t gw = words_for(U, w_gap), cw = words_for(U, w_cnt);
@@ -229,73 +109,11 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
     }
 
     // ---- undo delta + run-length coding (Sec. 4.3)
-    stage_words<DecodeSmem<ITEMS>::kSteps>(words, rec + 2, gw + cw, lane);
-    wave_lds_sync();
-    uint32_t g1[ITEMS], c1[ITEMS];
-    uint32_t gs = 0, cs = 0;
-    {
-        const uint32_t gm = low_mask(w_gap), cm = low_mask(w_cnt);
-#pragma unroll
-        for (int j = 0; j < ITEMS; j++) {
-            uint32_t i = lane * ITEMS + j;
-            g1[j] = i < U ? extract(words, i, w_gap, gm) + 1u : 0u;
-            c1[j] = i < U ? extract(words + gw, i, w_cnt, cm) + 1u : 0u;
-            gs += g1[j];
-            cs += c1[j];
-        }
-    }
-    const uint32_t gincl = wave_incl_scan_u32(gs), cincl = wave_incl_scan_u32(cs);
-    const uint32_t gtot = (uint32_t)__shfl((int)gincl, 63), ctot = (uint32_t)__shfl((int)cincl, 63);
-    // largest ID = sum(gap+1) - 1 must fit K*KF bits; run lengths sum to nb
-    if (ctot != nb || gtot == 0 || gtot - 1u >= (1u << (K * KF))) {
+    if (!expand_runs<ITEMS, DecodeSmem<ITEMS>::kSteps>(rec, U, w_gap, w_cnt, gw, cw, nb, K * KF,
+                                                       lane, sm.buf)) {
         if (lane == 0) *a.err = 1u;
         return;
     }
-    // mark run starts with their ID; IDs increase with position, so a prefix
-    // maximum over positions gives every position its ID
-    wave_lds_sync();  // the packed gaps and counts are read; `keys` reuses them
-    for (uint32_t p = lane; p < B; p += 64) keys[pad_addr<ITEMS>(p)] = 0u;
-    wave_lds_sync();
-    {
-        uint32_t u = gincl - gs, st = cincl - cs;
-#pragma unroll
-        for (int j = 0; j < ITEMS; j++) {
-            uint32_t i = lane * ITEMS + j;
-            if (i < U) {
-                u += g1[j];
-                keys[pad_addr<ITEMS>(st)] = u - 1u;
-                st += c1[j];
-            }
-        }
-    }
-    wave_lds_sync();
-    {
-        uint32_t key[ITEMS];
-        uint32_t run = 0;
-        const uint4* kb = reinterpret_cast<const uint4*>(keys + lane * (ITEMS + 4));
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-            uint4 t = kb[g];
-            run = max(run, t.x);
-            key[4 * g + 0] = run;
-            run = max(run, t.y);
-            key[4 * g + 1] = run;
-            run = max(run, t.z);
-            key[4 * g + 2] = run;
-            run = max(run, t.w);
-            key[4 * g + 3] = run;
-        }
-        uint32_t carry = wave_incl_max_u32(run);
-        carry = (uint32_t)__shfl_up((int)carry, 1);
-        if (lane == 0) carry = 0;
-        wave_lds_sync();
-        uint4* kw = reinterpret_cast<uint4*>(keys + lane * (ITEMS + 4));
-#pragma unroll
-        for (int g = 0; g < G; g++)
-            kw[g] = make_uint4(max(key[4 * g], carry), max(key[4 * g + 1], carry),
-                               max(key[4 * g + 2], carry), max(key[4 * g + 3], carry));
-    }
-    wave_lds_sync();
     // striped positions of this lane: p = 256 g + 4 lane + e
     uint32_t skey[ITEMS];
 #pragma unroll

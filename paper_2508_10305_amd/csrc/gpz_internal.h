@@ -280,6 +280,8 @@ hipError_t launch_encode64(const EncodeArgs& a, hipStream_t s);
 hipError_t launch_scan(const ScanArgs& a, hipStream_t s);
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s);
+// float64 streams of block size 1024.
+hipError_t launch_decode64(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStream_t s);
 // nzero words at `zero` cleared and the range keys (nkeys minima, nkeys
 // maxima) set to the identities of atomicMin / atomicMax, in one launch.

@@ -90,3 +90,32 @@ def test_raw_blocks_and_empty_range(gpz, orc):
     check(gpz, orc, [huge, bits], 1e-3, label="raw")
     check(gpz, orc, [np.full(n, 2.5), np.full(n, np.nan), np.full(n, np.inf)], 1e-3, label="constant")
     check(gpz, orc, [np.full(n, 2.5), rng.standard_normal(n), huge], 1e-3, label="one raw field")
+
+
+def test_damaged_streams_are_refused_as_by_the_oracle(gpz, orc):
+    """One word of a stream changed at a time (headers, tables, lengths, record
+    headers, field words, outlier lists, payloads): the GPU accepts it exactly
+    when the oracle does, and then decodes the same bits."""
+    rng = np.random.default_rng(11)
+    n, F = 2500, 3
+    host = mixed(n, F + 1, rng)[1:]  # wide, half wide, non-finite values
+    ref, _ = orc.compress(host, 1e-3)
+    words = ref.view(np.uint32)
+    recs = 8 + 2 + F + 3  # header, one superblock, bounds, three lengths
+    at = list(range(recs)) + [recs, recs + 1, recs + 2, recs + 3]
+    at += sorted(rng.choice(np.arange(recs, words.size), 120, replace=False).tolist())
+    for k in at:
+        bad = words.copy()
+        bad[k] ^= np.uint32(1) << np.uint32(rng.integers(0, 32))
+        print(f"[case] damaged word {k}", flush=True)
+        want = orc.decompress_status(bad.view(np.uint8), n, F, f64=True)
+        dev = torch.from_numpy(bad.view(np.uint8)).cuda()
+        try:
+            out = gpz.decompress_f64(dev, n, F)
+            got = 0
+        except gpz.GpzError as e:
+            got = e.code
+        assert (got == 0) == (want == 0), (k, got, want)
+        if got == 0:
+            for o, r in zip(out, orc.decompress(bad.view(np.uint8), n, F, f64=True)):
+                assert (o.cpu().numpy().view(np.uint64) == r.view(np.uint64)).all(), k
