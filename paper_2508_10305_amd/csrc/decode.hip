@@ -11,6 +11,7 @@
 // between its lanes is ordered by wave_lds_sync().  Every read of the record
 // is checked against its length first; a malformed record sets the error
 // flag and the block is skipped.
+#include "decode64.h"
 #include "decode_block.h"
 
 namespace gpz {

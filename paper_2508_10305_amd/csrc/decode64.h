@@ -9,6 +9,8 @@
 // the generic decoder (one lane per 4 positions, each reading its bits from
 // memory), 125 here, of which about 45 are the call's launches and waits;
 // with every field on 64-bit steps 323 -> 159.
+#pragma once
+
 #include "decode_block.h"
 
 namespace gpz {

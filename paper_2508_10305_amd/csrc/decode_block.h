@@ -1,5 +1,5 @@
 // Pieces of the wave-per-block decoders (float32 in decode.hip, float64 in
-// decode64.hip): staging of packed arrays in LDS, extraction, location and
+// decode64.h): staging of packed arrays in LDS, extraction, location and
 // checks of a block's record, expansion of its segment IDs.
 #pragma once
 

@@ -16,6 +16,7 @@
 // global-memory stores of the block must be ordered.  Full blocks take a path
 // without per-item bounds checks; only the last block of a snapshot can be
 // partial.
+#include "encode64.h"
 #include "encode_block.h"
 
 namespace gpz {

@@ -16,6 +16,8 @@
 // CU.  8M x 6 at a bound float32 meets: 389 us with the generic encoder (four
 // waves a block, some forty workgroup barriers), 128 here; at one it does not
 // (every field wide): the whole call 707 -> 442 us.
+#pragma once
+
 #include "encode_block.h"
 #include "generic_block.h"
 

@@ -1,5 +1,5 @@
 // Pieces of the wave-per-block encoders (float32 in encode.hip, float64 in
-// encode64.hip): quantizer of float32 fields, stable in-block radix sort,
+// encode64.h): quantizer of float32 fields, stable in-block radix sort,
 // run-length tables, fixed-length packing, for one block of B = 64 * ITEMS
 // particles per wave64.  Lane l owns the ITEMS consecutive particles
 // [l*ITEMS, (l+1)*ITEMS) ("blocked"); LDS traffic between the lanes of the

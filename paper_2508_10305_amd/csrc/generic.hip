@@ -1,7 +1,7 @@
 // Generic block kernels: the cases the wave-per-block kernels leave out.
 //  - float64 fields (Sec. 5.1: each field of each block is down-cast to
 //    float32 when that meets the bound, else quantized in double) at block
-//    sizes other than 1024 (encode64.hip has those);
+//    sizes other than 1024 (encode64.h has those);
 //  - fields of a block whose grid needs more than 24 bits (Sec. 5.3: 64-bit
 //    intermediates when the value range needs them): the fast encoder
 //    leaves such blocks on a list for the encoder here (the fast decoder
