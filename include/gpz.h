@@ -170,7 +170,9 @@ int gpz_decompress_async(const void *d_in, uint64_t in_bytes, float *const *h_fi
 /* Device workspace of the reporting calls below (gpz_bound_check,
  * gpz_error_stats, gpz_stream_stats, gpz_field_range): 32 bytes per field
  * plus 64, rounded up to 256.  0 for F outside 1..64.  With a workspace these
- * calls allocate nothing; with d_ws == NULL the library allocates and frees
+ * calls allocate no device memory (a synchronous call may borrow one of at
+ * most 64 pages of 4 KB of pinned host memory that the process makes as calls
+ * overlap; none, and all calls work as before); with d_ws == NULL the library allocates and frees
  * one per call (GPZ_ENOMEM if it cannot).  A workspace may be reused by
  * calls that run one after the other on one stream, not by concurrent ones. */
 uint64_t gpz_stats_workspace_bytes(uint32_t nfields);

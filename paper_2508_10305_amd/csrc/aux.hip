@@ -126,6 +126,11 @@ __global__ void fill_u32(uint32_t* p, uint32_t value, uint64_t count) {
     if (i < count) p[i] = value;
 }
 
+__global__ __launch_bounds__(256) void copy_words(uint32_t* dst, const uint32_t* src,
+                                                  uint32_t words) {
+    for (uint32_t i = threadIdx.x; i < words; i += 256) dst[i] = src[i];
+}
+
 struct BoundArgs {
     const float* orig[kMaxFields];
     const float* recon[kMaxFields];
@@ -667,6 +672,11 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStrea
     if (count == 0) return hipSuccess;
     uint64_t blocks = (count + 255) / 256;
     hipLaunchKernelGGL(fill_u32, dim3((uint32_t)blocks), dim3(256), 0, s, p, value, count);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_words(uint32_t* dst, const uint32_t* src, uint32_t words, hipStream_t s) {
+    hipLaunchKernelGGL(copy_words, dim3(1), dim3(256), 0, s, dst, src, words);
     return hipGetLastError();
 }
 

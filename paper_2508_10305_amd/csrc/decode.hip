@@ -229,6 +229,7 @@ template <int ITEMS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void decode_blocks(DecodeArgs a) {
     __shared__ __align__(16) DecodeShared<ITEMS> sm;
     decode_block<ITEMS>(a, blockIdx.x, sm);
+    post_header(a);
 }
 
 // Persistent decoder over the blocks of many streams: each wave takes `tile`

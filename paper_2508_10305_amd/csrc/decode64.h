@@ -191,6 +191,7 @@ __device__ __forceinline__ void decode_block64(const DecodeArgs& a, uint32_t b, 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void decode_blocks64(DecodeArgs a) {
     __shared__ __align__(16) uint32_t words[kBuf64];
     decode_block64(a, blockIdx.x, words);
+    post_header(a);
 }
 
 }  // namespace

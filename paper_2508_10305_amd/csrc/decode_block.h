@@ -74,6 +74,12 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
     return v;
 }
 
+// The first workgroup's copy of the stream's header for the host.
+__device__ __forceinline__ void post_header(const DecodeArgs& a) {
+    if (a.header && blockIdx.x == 0 && threadIdx.x < kHeaderWords)
+        a.header[threadIdx.x] = a.in[threadIdx.x];
+}
+
 // Whether the stream's header or eb table does not describe the stream the
 // caller asked for (lane k < 8 checks header word k, every lane a share of
 // the eb table).  `types`: the value-type flag asked for (0 float32, 1

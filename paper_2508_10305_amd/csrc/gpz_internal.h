@@ -100,7 +100,8 @@ struct DecodeArgs {
     uint64_t prefix;       // words before the record area
     uint32_t* err;         // set nonzero on a malformed record
     uint32_t exact;        // in_words is the exact stream length (else an upper bound)
-    uint32_t f64;          // float64 stream: y[f] are double* (generic decoder only)
+    uint32_t f64;          // float64 stream: y[f] are double*
+    uint32_t* header;      // nullable: receives the stream's header words
 };
 
 // ------------------------------------------------------------ wave64 primitives
@@ -282,6 +283,8 @@ hipError_t launch_copy(const CopyArgs& a, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s);
 // float64 streams of block size 1024.
 hipError_t launch_decode64(const DecodeArgs& a, hipStream_t s);
+// Device words to pinned host memory (or any device address).
+hipError_t launch_copy_words(uint32_t* dst, const uint32_t* src, uint32_t words, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t count, hipStream_t s);
 // nzero words at `zero` cleared and the range keys (nkeys minima, nkeys
 // maxima) set to the identities of atomicMin / atomicMax, in one launch.
