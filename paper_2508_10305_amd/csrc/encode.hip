@@ -505,12 +505,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void en
 }
 
 // The same with no early fields beside the key fields (EARLY = 0) and the
-// sort's lean scan: at most 168 VGPRs, three waves per SIMD instead of two.
-// At B = 1024 this is faster on every workload measured (cosmology 64M x 6
-// -4 %, md 32M x 6 -4 %, LiDAR 100M x 3 -13 %): the late fields' loads are
-// hidden by the third wave.
+// sort's lean scan: at most 168 VGPRs, three waves per SIMD instead of two
+// (four below B = 1024, where 103 VGPRs and 9 KB of LDS allow it).  Up to
+// B = 1024 this is faster on every workload measured: the late fields' loads
+// are hidden by the additional wave (B = 1024: cosmology 64M x 6 -4 %, md
+// 32M x 6 -4 %, LiDAR 100M x 3 -13 %; B = 512, cosmology 4M x 6: 72 -> 62 us,
+// B = 256 within 1 %).  At B = 2048 both spill.
 template <int ITEMS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void encode_blocks_lean(EncodeArgs a) {
+constexpr bool kLean = ITEMS <= 16;
+template <int ITEMS>
+constexpr int kWaves = ITEMS == 16 ? 3 : ITEMS < 16 ? 4 : 2;
+
+template <int ITEMS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<ITEMS>))) void encode_blocks_lean(EncodeArgs a) {
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
     const uint32_t b = blockIdx.x;
@@ -549,7 +556,7 @@ void launch_encode_items(const EncodeArgs& a, bool single_pass, hipStream_t s) {
     // last block the checked one, alongside them (not in a second launch
     // that would wait for the first)
     if (a.nblocks == 0) return;
-    if constexpr (ITEMS == 16)
+    if constexpr (kLean<ITEMS>)
         hipLaunchKernelGGL(encode_blocks_lean<ITEMS>, dim3(a.nblocks), dim3(64), 0, s, a);
     else
         hipLaunchKernelGGL(encode_blocks<ITEMS>, dim3(a.nblocks), dim3(64), 0, s, a);
@@ -588,10 +595,10 @@ template <int ITEMS>
 constexpr bool kDirectTails = ITEMS <= 16;
 
 template <int ITEMS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ITEMS == 16 ? 3 : 2))) void encode_batch_direct(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<ITEMS>))) void encode_batch_direct(
     const EncodeArgs* __restrict__ jobs, const BatchLaunch* __restrict__ L) {
     constexpr uint32_t B = 64 * ITEMS;
-    constexpr int EARLY = ITEMS == 16 ? 0 : 3;
+    constexpr int EARLY = kLean<ITEMS> ? 0 : 3;
     __shared__ EncodeSmem<ITEMS> sm;
     const uint32_t g = blockIdx.x;
     if (g >= (kDirectTails<ITEMS> ? L->total_blocks : L->total_full)) return;
@@ -611,7 +618,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ITEMS == 16 
 
 // The partial last block of each snapshot that has one.
 template <int ITEMS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ITEMS == 16 ? 3 : 2))) void encode_batch_tails(const EncodeArgs* __restrict__ jobs,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<ITEMS>))) void encode_batch_tails(const EncodeArgs* __restrict__ jobs,
                                                          const BatchLaunch* __restrict__ L) {
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
@@ -620,7 +627,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ITEMS == 16 
         const EncodeArgs& a = jobs[__builtin_amdgcn_readfirstlane((int)L->tail_jobs[t])];
         const uint32_t b = a.nblocks - 1;
         const uint32_t nb = (uint32_t)(a.n - (uint64_t)b * B);
-        encode_block<ITEMS, false, false, ITEMS == 16 ? 0 : 3>(a, b, nb, sm.buf);
+        encode_block<ITEMS, false, false, kLean<ITEMS> ? 0 : 3>(a, b, nb, sm.buf);
         __syncthreads();
     }
 }

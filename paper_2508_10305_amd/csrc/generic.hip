@@ -606,10 +606,12 @@ hipError_t launch_encode_deferred_then_scan(const EncodeArgs& a, const ScanArgs&
     // two workgroups per CU: few empty workgroups when nothing is deferred
     const uint32_t g = 2u * device_cu_count();
     const dim3 grid(a.nblocks < g ? (a.nblocks ? a.nblocks : 1u) : g), block(kT);
+    // (the wave-per-block encoder's blocks hold at most 2048 particles; with
+    // the 57 KB of LDS of 4096 an empty walk took 30 us, with 2048's 29)
     if (a.B <= 1024)
         hipLaunchKernelGGL(gen_encode_deferred_then_scan<1024>, grid, block, 0, s, a, sa, done);
     else
-        hipLaunchKernelGGL(gen_encode_deferred_then_scan<4096>, grid, block, 0, s, a, sa, done);
+        hipLaunchKernelGGL(gen_encode_deferred_then_scan<2048>, grid, block, 0, s, a, sa, done);
     return hipGetLastError();
 }
 
@@ -626,7 +628,7 @@ hipError_t launch_encode_generic_batch(const EncodeArgs* jobs, const BatchLaunch
                                        uint32_t max_blocks, hipStream_t s) {
     const dim3 grid(walk_grid(max_blocks)), block(kT);
     if (B <= 1024) hipLaunchKernelGGL(gen_encode_deferred_batch<1024>, grid, block, 0, s, jobs, L);
-    else hipLaunchKernelGGL(gen_encode_deferred_batch<4096>, grid, block, 0, s, jobs, L);
+    else hipLaunchKernelGGL(gen_encode_deferred_batch<2048>, grid, block, 0, s, jobs, L);
     return hipGetLastError();
 }
 
