@@ -41,7 +41,7 @@ struct gpz_batch {
     uint32_t* d_errors = nullptr;  // decode error flag per job
     // blocks left to the generic encoder (their grid needs 64-bit steps):
     // one list per job inside d_defer, its length and the job's wide-record
-    // flag (d_dcount and d_wide are contiguous, cleared by one fill)
+    // flag
     uint32_t* d_defer = nullptr;
     uint32_t* d_dcount = nullptr;
     uint32_t* d_wide = nullptr;
@@ -123,9 +123,9 @@ uint64_t jobs_workspace(const gpz_job* jobs, uint32_t njobs, uint32_t B) {
 int to_status(hipError_t e) { return e == hipSuccess ? GPZ_OK : GPZ_EDEVICE; }
 
 int enqueue_compress(gpz_batch* b, hipStream_t s) {
-    int rc = to_status(launch_fill_u32(b->d_counters, 0u, 1, s));
-    if (rc == GPZ_OK) rc = to_status(launch_fill_u32(b->d_supsum, 0u, b->max_super + 1, s));
-    if (rc == GPZ_OK) rc = to_status(launch_fill_u32(b->d_dcount, 0u, 2ull * b->max_jobs, s));
+    // deferred counts, wide flags, superblock sums and the encode queue head
+    // in one fill
+    int rc = to_status(launch_fill_u32(b->d_dcount, 0u, b->d_counters + 1 - b->d_dcount, s));
     if (rc == GPZ_OK) rc = to_status(launch_encode_batch(b->d_enc, b->d_launch, b->shape, s));
     if (rc == GPZ_OK)
         rc = to_status(launch_encode_generic_batch(b->d_enc, b->d_launch, b->p.block_size,
@@ -136,8 +136,8 @@ int enqueue_compress(gpz_batch* b, hipStream_t s) {
 }
 
 int enqueue_decompress(gpz_batch* b, hipStream_t s) {
-    int rc = to_status(launch_fill_u32(b->d_counters + 1, 0u, 1, s));
-    if (rc == GPZ_OK) rc = to_status(launch_fill_u32(b->d_errors, 0u, b->max_jobs, s));
+    // the decode queue head and the error flags behind it
+    int rc = to_status(launch_fill_u32(b->d_counters + 1, 0u, 1ull + b->max_jobs, s));
     if (rc == GPZ_OK) rc = to_status(launch_decode_batch(b->d_dec, b->d_launch, b->shape, s));
     return rc;
 }
@@ -379,15 +379,19 @@ int gpz_batch_create(gpz_batch** out, const gpz_job* jobs, uint32_t njobs, const
     const uint64_t o_fp = take(4ull * (mj + 1));
     const uint64_t o_bp = take(4ull * (mj + 1));
     const uint64_t o_tail = take(4ull * (mj + 1));
-    const uint64_t o_cnt = take(8);
+    // what a compression clears (deferred counts, wide flags, superblock sums,
+    // encode queue head), then what a decompression clears (decode queue
+    // head, error flags), contiguous: one fill each (three fills more cost a
+    // round of 24 snapshots 6 us of 364, one of 8 smaller ones 5 of 90)
+    const uint64_t o_dcount = take(8ull * mj + 4 * ms + 4 + 8 + 4ull * mj);
+    const uint64_t o_sups = o_dcount + 8ull * mj;
+    const uint64_t o_cnt = o_sups + 4 * ms + 4;
+    const uint64_t o_err = o_cnt + 8;
     const uint64_t o_lens = take(4 * mb + 4);
-    const uint64_t o_sups = take(4 * ms + 4);
     const uint64_t o_supo = take(8 * ms + 8);
     const uint64_t o_tot = take(8ull * mj);
     const uint64_t o_sizes = take(8ull * mj);
-    const uint64_t o_err = take(4ull * mj);
     const uint64_t o_defer = take(4 * mb + 4);
-    const uint64_t o_dcount = take(8ull * mj);  // counts, then wide flags
     if (hipMalloc(&b->tables, o) != hipSuccess) {
         delete b;
         return GPZ_ENOMEM;
@@ -411,7 +415,7 @@ int gpz_batch_create(gpz_batch** out, const gpz_job* jobs, uint32_t njobs, const
     b->d_defer = reinterpret_cast<uint32_t*>(base + o_defer);
     b->d_dcount = reinterpret_cast<uint32_t*>(base + o_dcount);
     b->d_wide = b->d_dcount + mj;
-    b->upload_bytes = o_cnt;  // the tables and launch descriptor come first
+    b->upload_bytes = o_dcount;  // the tables and launch descriptor come first
     if (hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&b->uploaded, hipEventDisableTiming) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&b->h_tables), b->upload_bytes) != hipSuccess) {

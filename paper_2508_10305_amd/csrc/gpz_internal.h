@@ -327,10 +327,28 @@ uint32_t device_cu_count();
 // block g of the flattened list belongs to the job j with
 // prefix[j] <= g < prefix[j+1] (found by a uniform binary search).
 
-// g must be wave-uniform; the result is returned through readfirstlane so
-// the compiler keeps it (and the job arguments it indexes) in scalar registers.
+// g must be wave-uniform, all 64 lanes active; the result is wave-uniform, so
+// the compiler keeps it (and the job arguments it indexes) in scalar
+// registers.  Up to 256 jobs each lane compares up to four entries of the
+// prefix at once, for one memory round trip; a binary search, whose steps
+// depend on one another, took five at 24 jobs and eight at 256 (24 snapshots,
+// 16M particles x 6: encode 185 -> 181 us, copy 47 -> 46).
 __device__ __forceinline__ uint32_t find_job(const uint32_t* __restrict__ prefix, uint32_t njobs,
                                              uint32_t g) {
+    if (njobs <= 256) {
+        // jobs whose blocks all come before g
+        const uint32_t lane = lane_id();
+        uint32_t v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) {
+            const uint32_t i = 64 * k + lane;
+            v[k] = i < njobs ? prefix[i + 1] : 0xFFFFFFFFu;
+        }
+        uint32_t j = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) j += (uint32_t)__builtin_popcountll(__ballot(v[k] <= g));
+        return j;
+    }
     uint32_t lo = 0, hi = njobs;
     while (hi - lo > 1) {
         uint32_t mid = (lo + hi) >> 1;
