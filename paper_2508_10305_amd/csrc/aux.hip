@@ -173,10 +173,14 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 
 constexpr uint32_t kCheckChunk = 1024;  // positions per wave step
 constexpr int kCheckItems = kCheckChunk / 64;
-// Workgroups per CU: 128 registers let four waves share a SIMD, whose loads
+// Two workgroups of eight waves per CU: 128 registers let four waves share a SIMD, whose loads
 // (8 KB each) cover the memory's latency without a prefetch (with one, which
 // spilled at this occupancy, a whole 16M x 6 report took 295 us; 238 without).
-constexpr uint32_t kCheckGroups = 4;
+// Eight waves share a workgroup's atomics at the end, which run one after the
+// other on a field's words: 128 us at 16M x 6, with four waves 141, with
+// sixteen 128 (and fewer CUs at work on a small snapshot).
+constexpr uint32_t kCheckWaves = 8;
+constexpr uint32_t kCheckGroups = 2;
 
 // Values 256k + 4 lane + e of a chunk that starts at p (whole, or those whose
 // bit is set in `live`; the others are 0).
@@ -215,15 +219,15 @@ __device__ __forceinline__ void check_load(const float* p, bool whole, uint32_t 
 // largest error, the finite range and the presence of a NaN are tested once
 // per lane and chunk (a lane's sum is NaN exactly when one of its differences
 // is), and only chunks that fail a test count pairs one by one or reduce
-// across the wave.  16M x 6 with a permutation (0.83 GB): 141 us, 5.9 TB/s;
+// across the wave.  16M x 6 with a permutation (0.83 GB): 128 us, 6.5 TB/s;
 // the check that gathered the originals from memory took 274 us and the
 // separate range pass another 100.
 template <bool STATS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void bound_check_kernel(BoundArgs a) {
-    __shared__ float win[4][kCheckChunk];
-    __shared__ double sm[4][kMaxFields], ss[4][kMaxFields];
-    __shared__ unsigned long long sv[4][kMaxFields];
-    __shared__ int skn[4][kMaxFields], skx[4][kMaxFields];
+__global__ __launch_bounds__(64 * kCheckWaves) __attribute__((amdgpu_waves_per_eu(4))) void bound_check_kernel(BoundArgs a) {
+    __shared__ float win[kCheckWaves][kCheckChunk];
+    __shared__ double sm[kCheckWaves][kMaxFields], ss[kCheckWaves][kMaxFields];
+    __shared__ unsigned long long sv[kCheckWaves][kMaxFields];
+    __shared__ int skn[kCheckWaves][kMaxFields], skx[kCheckWaves][kMaxFields];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     float* const mywin = win[w];
@@ -234,7 +238,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
     skx[w][lane] = (int)0x80000000;
     wave_lds_sync();
     const uint64_t nchunks = (a.n + kCheckChunk - 1) / kCheckChunk;
-    for (uint64_t c = (uint64_t)blockIdx.x * 4 + w; c < nchunks; c += (uint64_t)gridDim.x * 4) {
+    for (uint64_t c = (uint64_t)blockIdx.x * kCheckWaves + w; c < nchunks;
+         c += (uint64_t)gridDim.x * kCheckWaves) {
         const uint64_t c0 = c * kCheckChunk;
         const uint64_t left = a.n - c0;
         const bool whole = left >= kCheckChunk;
@@ -380,11 +385,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
         }
     }
     __syncthreads();
-    for (uint32_t f = threadIdx.x; f < a.F; f += 256) {
+    for (uint32_t f = threadIdx.x; f < a.F; f += 64 * kCheckWaves) {
         unsigned long long tv = 0;
         double tm = 0.0, tq = 0.0;
         int kn = 0x7FFFFFFF, kx = (int)0x80000000;
-        for (int i = 0; i < 4; i++) {
+        for (uint32_t i = 0; i < kCheckWaves; i++) {
             tv += sv[i][f];
             tm = fmax(tm, sm[i][f]);
             tq += ss[i][f];
@@ -574,9 +579,13 @@ __device__ __forceinline__ void range_load(const RangeChunk& r, uint64_t chunk, 
 
 // Field range over finite values.  The 16-byte vectors of every field are cut
 // into chunks of U * 256 vectors (chunk c belongs to field c / cpf);
-// workgroup g takes chunks g, g + gridDim.x, ...  The loads of the next chunk
-// are issued before the current one is reduced (two register buffers), so
-// the memory stays busy while a wave computes.  Positions past a field's
+// every workgroup takes a contiguous range of them, so that it ends one field,
+// rarely two, and each field's keys see few of the workgroups' atomics, which
+// run one after the other (with chunks g, g + gridDim.x, ... every workgroup
+// ended every field: 1M x 6 took 43 us for 24 MB, 17 now; 20M x 3 65 -> 47;
+// 64M x 6 254 -> 227, 6.8 TB/s).  The loads of the next chunk are issued
+// before the current one is reduced (two register buffers), so the memory
+// stays busy while a wave computes.  Positions past a field's
 // last whole vector load as NaN, which the finite test skips.  Every wave
 // follows the same chunk sequence, so a change of field is
 // workgroup-uniform: the running extrema are then folded into the field's
@@ -589,17 +598,19 @@ __global__ __launch_bounds__(256) void field_range_kernel(RangeArgs a) {
     const uint64_t chunk = (uint64_t)U * 256;
     const uint64_t total = a.cpf * a.F;
     int mn = 0x7FFFFFFF, mx = (int)0x80000000;
-    uint64_t c = blockIdx.x;
-    if (c < total) {
+    const uint64_t each = (total + gridDim.x - 1) / gridDim.x;
+    uint64_t c = blockIdx.x * each;
+    const uint64_t end = c + each < total ? c + each : total;
+    if (c < end) {
         uint32_t cur = 0xFFFFFFFFu;
         RangeChunk r = range_chunk(a, c, chunk);
         f32x4 v[U];
         range_load<U>(r, chunk, v);
         for (;;) {
-            const uint64_t cn = c + gridDim.x;
+            const uint64_t cn = c + 1;
             RangeChunk rn = r;
             f32x4 w[U];
-            if (cn < total) {
+            if (cn < end) {
                 rn = range_chunk(a, cn, chunk);
                 range_load<U>(rn, chunk, w);
             }
@@ -611,7 +622,7 @@ __global__ __launch_bounds__(256) void field_range_kernel(RangeArgs a) {
             }
 #pragma unroll
             for (int k = 0; k < U; k++) range_take4(v[k], mn, mx);
-            if (cn >= total) break;
+            if (cn >= end) break;
             c = cn;
             r = rn;
 #pragma unroll
@@ -722,13 +733,15 @@ hipError_t launch_bound_check(const float* const* orig, const float* const* reco
     a.maxerr_bits = maxerr_bits;
     a.sumsq = sumsq;
     a.keys = keys;
-    const uint64_t need = ((n + kCheckChunk - 1) / kCheckChunk + 3) / 4;
+    const uint64_t need = ((n + kCheckChunk - 1) / kCheckChunk + kCheckWaves - 1) / kCheckWaves;
     const uint64_t most = (uint64_t)kCheckGroups * device_cu_count();
     const uint64_t groups = need < 1 ? 1 : (need < most ? need : most);
     if (sumsq)
-        hipLaunchKernelGGL(bound_check_kernel<true>, dim3((uint32_t)groups), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(bound_check_kernel<true>, dim3((uint32_t)groups), dim3(64 * kCheckWaves),
+                           0, s, a);
     else
-        hipLaunchKernelGGL(bound_check_kernel<false>, dim3((uint32_t)groups), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(bound_check_kernel<false>, dim3((uint32_t)groups), dim3(64 * kCheckWaves),
+                           0, s, a);
     return hipGetLastError();
 }
 
@@ -774,35 +787,24 @@ uint32_t device_cu_count() {
     return (uint32_t)c;
 }
 
-hipError_t launch_field_range_shape(const float* const* x, uint64_t n, uint32_t F, int* keys,
-                                    uint32_t groups_per_cu, uint32_t unroll, hipStream_t s) {
+hipError_t launch_field_range(const float* const* x, uint64_t n, uint32_t F, int* keys,
+                              hipStream_t s) {
+    // two workgroups per CU, eight 16-byte loads in flight per lane and buffer
+    // (2 x 4 took 23, 50 and 238 us at the three sizes above, 4 x 4 26, 46 and
+    // 228, 4 x 2 32, 55 and 230)
+    constexpr int kLoads = 8;
     RangeArgs a{};
     for (uint32_t f = 0; f < F; f++) a.x[f] = x[f];
     a.n = n;
     a.F = F;
     a.keys = keys;
-    const uint64_t chunk = (uint64_t)unroll * 256;
+    const uint64_t chunk = (uint64_t)kLoads * 256;
     a.cpf = (n / 4 + chunk - 1) / chunk;
     if (a.cpf == 0) a.cpf = 1;  // workgroup 0 still takes the loose elements
-    uint64_t groups = (uint64_t)groups_per_cu * device_cu_count();
+    uint64_t groups = 2ull * device_cu_count();
     if (groups > a.cpf * F) groups = a.cpf * F;  // never more than the chunks
-    if (groups == 0) groups = 1;
-    const dim3 g((uint32_t)groups), b(256);
-    switch (unroll) {
-        case 2: hipLaunchKernelGGL(field_range_kernel<2>, g, b, 0, s, a); break;
-        case 4: hipLaunchKernelGGL(field_range_kernel<4>, g, b, 0, s, a); break;
-        case 8: hipLaunchKernelGGL(field_range_kernel<8>, g, b, 0, s, a); break;
-        case 16: hipLaunchKernelGGL(field_range_kernel<16>, g, b, 0, s, a); break;
-        default: return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL(field_range_kernel<kLoads>, dim3((uint32_t)groups), dim3(256), 0, s, a);
     return hipGetLastError();
-}
-
-hipError_t launch_field_range(const float* const* x, uint64_t n, uint32_t F, int* keys,
-                              hipStream_t s) {
-    // two workgroups per CU, four 16-byte loads in flight per lane: the best
-    // shape of a sweep over 1-16 workgroups per CU and 2-16 loads (64M x 6)
-    return launch_field_range_shape(x, n, F, keys, 2, 4, s);
 }
 
 }  // namespace gpz

@@ -301,10 +301,6 @@ hipError_t launch_stream_stats(const uint32_t* in, uint64_t in_words, uint64_t n
                                uint32_t* err, hipStream_t s);
 hipError_t launch_field_range(const float* const* x, uint64_t n, uint32_t F, int* keys,
                               hipStream_t s);
-// The same with an explicit launch shape: workgroups per CU and 16-byte
-// loads in flight per lane (2, 4, 8 or 16).
-hipError_t launch_field_range_shape(const float* const* x, uint64_t n, uint32_t F, int* keys,
-                                    uint32_t groups_per_cu, uint32_t unroll, hipStream_t s);
 // Generic 256-lane-per-block kernels (float64 fields, fields needing 64-bit
 // grid steps, any block size).  deferred_only: the blocks the wave-per-block
 // encoder left on its list; otherwise every block.  The decoder takes every

@@ -81,3 +81,25 @@ def test_report_at_chunk_edges(gpz, orc, n, F, shift, kind, special):
         assert st["max_abs_err"].tolist() == rm.tolist()
         assert (st["range"].view(np.uint32) == orc.field_range(hx).view(np.uint32)).all()
         assert np.allclose(st["sum_sq"], ref["sum_sq"], rtol=n * 2.0 ** -52, atol=0)
+
+
+@pytest.mark.parametrize("n,F,shift", [(1, 1, 0), (7, 3, 1), (8191, 2, 0), (8192, 1, 0), (8193, 2, 3),
+                                       (8192 * 3 + 5, 64, 2), (600_011, 5, 1), (8192 * 520, 1, 0)])
+def test_range_at_chunk_edges(gpz, n, F, shift):
+    """Every field's extremes are found wherever they lie: first, last and at
+    the ends of the 8192-value chunks, each workgroup's range of which ends in
+    the middle of a field."""
+    rng = np.random.default_rng(n + F)
+    for place in (0, n - 1, min(n - 1, 8191), n // 2):
+        host = [rng.standard_normal(n).astype(np.float32) for _ in range(F)]
+        for f, h in enumerate(host):
+            h[place] = 100.0 + f
+            h[n - 1 - place] = -100.0 - f
+            if n > 100:
+                h[n // 3] = (np.nan, np.inf, -np.inf)[f % 3]
+        dev = [torch.from_numpy(np.concatenate([np.full(shift, 1e9, np.float32), h])).cuda()[shift:]
+               for h in host]
+        got = gpz.field_range(dev, ws=gpz.stats_workspace(F))
+        for f, h in enumerate(host):
+            fin = h[np.isfinite(h)]
+            assert got[f].tolist() == [fin.min(), fin.max()], (n, f, place)
