@@ -178,17 +178,37 @@ def _torch():
     return torch
 
 
+# The calls below are on the path of every snapshot, however small, so they
+# build each argument once, without the objects torch.cuda.current_stream(),
+# ctypes.cast or ndarray.ctypes would make.
+_RAW_STREAM = None  # torch's handle-only form of current_stream, once looked up
+
+
 def _stream_handle(stream=None) -> int:
+    global _RAW_STREAM
+    if stream is not None:
+        return int(stream.cuda_stream)
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if _RAW_STREAM is None:
+        torch.cuda.current_stream()  # initializes the device
+        get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        _RAW_STREAM = ((lambda: get(device())) if get and device else
+                       (lambda: torch.cuda.current_stream().cuda_stream))
+    return int(_RAW_STREAM())
+
+
+_PTR_ARRAYS = [ctypes.c_void_p * max(1, n) for n in range(65)]
 
 
 def _ptr_array(tensors: Sequence) -> ctypes.Array:
-    arr = (ctypes.c_void_p * max(1, len(tensors)))()
-    for i, t in enumerate(tensors):
-        arr[i] = t.data_ptr()
-    return arr
+    n = len(tensors)
+    kind = _PTR_ARRAYS[n] if n <= 64 else ctypes.c_void_p * n
+    return kind(*[t.data_ptr() for t in tensors])
+
+
+def _address(a: np.ndarray) -> int:
+    return a.__array_interface__["data"][0]
 
 
 def _check_fields(fields: Sequence, n: Optional[int] = None, dtype=None):
@@ -237,6 +257,18 @@ def compress_workspace_bytes(n: int, nfields: int, p: Optional[Params] = None) -
     return int(_lib().gpz_compress_workspace_bytes(n, nfields, ctypes.byref(p) if p else None))
 
 
+def _compress_sync(fields: Sequence, n: int, F: int, eb, p: Params, out, ws, perm,
+                   stream) -> int:
+    ebs = _eb_array(eb, F)
+    nbytes = ctypes.c_uint64(0)
+    rc = _lib().gpz_compress(_ptr_array(fields), n, F, _address(ebs), ctypes.byref(p),
+                             out.data_ptr(), out.numel(), ctypes.byref(nbytes),
+                             perm.data_ptr() if perm is not None else None, ws.data_ptr(),
+                             ws.numel(), _stream_handle(stream))
+    _check(rc, "gpz_compress")
+    return nbytes.value
+
+
 class Compressor:
     """Reusable device buffers for repeated compression of one shape."""
 
@@ -254,23 +286,17 @@ class Compressor:
     def compress(self, fields: Sequence, eb, want_perm: bool = False, stream=None):
         """Synchronous compress; returns (stream view, perm view or None)."""
         n = _check_fields(fields, self.n)
-        ebs = _eb_array(eb, self.F)
-        nbytes = ctypes.c_uint64(0)
-        rc = _lib().gpz_compress(
-            ctypes.cast(_ptr_array(fields), ctypes.c_void_p), n, self.F,
-            ebs.ctypes.data_as(ctypes.c_void_p), ctypes.byref(self.p), self.out.data_ptr(),
-            self.out.numel(), ctypes.byref(nbytes), self.perm.data_ptr() if want_perm else None,
-            self.ws.data_ptr(), self.ws.numel(), _stream_handle(stream))
-        _check(rc, "gpz_compress")
-        return self.out[: nbytes.value], (self.perm[:n] if want_perm else None)
+        nbytes = _compress_sync(fields, n, self.F, eb, self.p, self.out, self.ws,
+                                self.perm if want_perm else None, stream)
+        return self.out[:nbytes], (self.perm[:n] if want_perm else None)
 
     def compress_async(self, fields: Sequence, eb, want_perm: bool = False, stream=None):
         """Enqueue only; the stream size lands in self.nbytes_dev."""
         n = _check_fields(fields, self.n)
         ebs = _eb_array(eb, self.F)
         rc = _lib().gpz_compress_async(
-            ctypes.cast(_ptr_array(fields), ctypes.c_void_p), n, self.F,
-            ebs.ctypes.data_as(ctypes.c_void_p), ctypes.byref(self.p), self.out.data_ptr(),
+            _ptr_array(fields), n, self.F,
+            _address(ebs), ctypes.byref(self.p), self.out.data_ptr(),
             self.out.numel(), self.nbytes_dev.data_ptr(),
             self.perm.data_ptr() if want_perm else None, self.ws.data_ptr(), self.ws.numel(),
             _stream_handle(stream))
@@ -281,11 +307,16 @@ def compress(fields: Sequence, eb, *, block_size: int = 1024, seg_bits: int = 3,
              key_fields: Optional[int] = None, want_perm: bool = False, stream=None,
              single_pass: bool = False):
     """Compress SoA float32 CUDA tensors; returns (uint8 CUDA tensor, perm or None)."""
+    torch = _torch()
     F = len(fields)
     p = params(F, block_size, seg_bits, key_fields, single_pass)
-    c = Compressor(fields[0].numel(), F, p, device=fields[0].device)
-    s, perm = c.compress(fields, eb, want_perm=want_perm, stream=stream)
-    return s.clone(), (perm.clone() if perm is not None else None)
+    n, dev = fields[0].numel(), fields[0].device
+    out = torch.empty(max_compressed_bytes(n, F, p), dtype=torch.uint8, device=dev)
+    ws = torch.empty(max(compress_workspace_bytes(n, F, p), 256), dtype=torch.uint8, device=dev)
+    perm = torch.empty(max(n, 1), dtype=torch.int32, device=dev) if want_perm else None
+    _check_fields(fields, n)
+    nbytes = _compress_sync(fields, n, F, eb, p, out, ws, perm, stream)
+    return out[:nbytes].clone(), (perm[:n] if want_perm else None)
 
 
 def decompress(stream_bytes, n: int, nfields: int, out: Optional[List] = None, ws=None,
@@ -300,7 +331,7 @@ def decompress(stream_bytes, n: int, nfields: int, out: Optional[List] = None, w
     if ws is None:
         ws = torch.empty(256, dtype=torch.uint8, device=stream_bytes.device)
     rc = _lib().gpz_decompress(stream_bytes.data_ptr(), stream_bytes.numel(),
-                               ctypes.cast(_ptr_array(out), ctypes.c_void_p), n, nfields,
+                               _ptr_array(out), n, nfields,
                                ws.data_ptr(), ws.numel(), _stream_handle(stream))
     _check(rc, "gpz_decompress")
     return out
@@ -309,7 +340,7 @@ def decompress(stream_bytes, n: int, nfields: int, out: Optional[List] = None, w
 def decompress_async(stream_bytes, n: int, nfields: int, out: List, err, p: Optional[Params] = None,
                      stream=None):
     rc = _lib().gpz_decompress_async(stream_bytes.data_ptr(), stream_bytes.numel(),
-                                     ctypes.cast(_ptr_array(out), ctypes.c_void_p), n, nfields,
+                                     _ptr_array(out), n, nfields,
                                      ctypes.byref(p) if p else None, err.data_ptr(),
                                      _stream_handle(stream))
     _check(rc, "gpz_decompress_async")
@@ -333,8 +364,8 @@ def compress_f64(fields: Sequence, eb, *, block_size: int = 1024, seg_bits: int 
     ebs = _eb_array(eb, F)
     nbytes = ctypes.c_uint64(0)
     rc = _lib().gpz_compress_f64(
-        ctypes.cast(_ptr_array(fields), ctypes.c_void_p), n, F,
-        ebs.ctypes.data_as(ctypes.c_void_p), ctypes.byref(p), out.data_ptr(), out.numel(),
+        _ptr_array(fields), n, F,
+        _address(ebs), ctypes.byref(p), out.data_ptr(), out.numel(),
         ctypes.byref(nbytes), perm.data_ptr() if want_perm else None, ws.data_ptr(), ws.numel(),
         _stream_handle(stream))
     _check(rc, "gpz_compress_f64")
@@ -353,7 +384,7 @@ def decompress_f64(stream_bytes, n: int, nfields: int, out: Optional[List] = Non
     if ws is None:
         ws = torch.empty(256, dtype=torch.uint8, device=stream_bytes.device)
     rc = _lib().gpz_decompress_f64(stream_bytes.data_ptr(), stream_bytes.numel(),
-                                   ctypes.cast(_ptr_array(out), ctypes.c_void_p), n, nfields,
+                                   _ptr_array(out), n, nfields,
                                    ws.data_ptr(), ws.numel(), _stream_handle(stream))
     _check(rc, "gpz_decompress_f64")
     return out
@@ -381,12 +412,12 @@ def bound_check(orig: Sequence, recon: Sequence, eb, perm=None, stream=None, ws=
     ebs = _eb_array(eb, F)
     viol = np.zeros(F, np.uint64)
     mx = np.zeros(F, np.float64)
-    rc = _lib().gpz_bound_check(ctypes.cast(_ptr_array(orig), ctypes.c_void_p),
-                                ctypes.cast(_ptr_array(recon), ctypes.c_void_p),
+    rc = _lib().gpz_bound_check(_ptr_array(orig),
+                                _ptr_array(recon),
                                 perm.data_ptr() if perm is not None else None, n, F,
-                                ebs.ctypes.data_as(ctypes.c_void_p),
-                                viol.ctypes.data_as(ctypes.c_void_p),
-                                mx.ctypes.data_as(ctypes.c_void_p), *_ws_args(ws),
+                                _address(ebs),
+                                _address(viol),
+                                _address(mx), *_ws_args(ws),
                                 _stream_handle(stream))
     _check(rc, "gpz_bound_check")
     return viol, mx
@@ -403,10 +434,10 @@ def error_stats(orig: Sequence, recon: Sequence, eb, perm=None, stream=None, ws=
     ebs = _eb_array(eb, F)
     res = (FieldError * F)()
     psnr = ctypes.c_double(0.0)
-    rc = _lib().gpz_error_stats(ctypes.cast(_ptr_array(orig), ctypes.c_void_p),
-                                ctypes.cast(_ptr_array(recon), ctypes.c_void_p),
+    rc = _lib().gpz_error_stats(_ptr_array(orig),
+                                _ptr_array(recon),
                                 perm.data_ptr() if perm is not None else None, n, F,
-                                ebs.ctypes.data_as(ctypes.c_void_p), res, ctypes.byref(psnr),
+                                _address(ebs), res, ctypes.byref(psnr),
                                 *_ws_args(ws), _stream_handle(stream))
     _check(rc, "gpz_error_stats")
     return {"violations": np.array([r.violations for r in res], np.uint64),
@@ -422,8 +453,8 @@ def stream_stats(stream_bytes, n: int, nfields: int, stream=None, ws=None):
     out = np.zeros(nfields, np.uint64)
     raw = np.zeros(1, np.uint64)
     rc = _lib().gpz_stream_stats(stream_bytes.data_ptr(), stream_bytes.numel(), n, nfields,
-                                 out.ctypes.data_as(ctypes.c_void_p),
-                                 raw.ctypes.data_as(ctypes.c_void_p), *_ws_args(ws),
+                                 _address(out),
+                                 _address(raw), *_ws_args(ws),
                                  _stream_handle(stream))
     _check(rc, "gpz_stream_stats")
     return out, int(raw[0])
@@ -434,8 +465,8 @@ def field_range(fields: Sequence, stream=None, ws=None) -> np.ndarray:
     F = len(fields)
     n = _check_fields(fields)
     mm = np.zeros(2 * F, np.float32)
-    rc = _lib().gpz_field_range(ctypes.cast(_ptr_array(fields), ctypes.c_void_p), n, F,
-                                mm.ctypes.data_as(ctypes.c_void_p), *_ws_args(ws),
+    rc = _lib().gpz_field_range(_ptr_array(fields), n, F,
+                                _address(mm), *_ws_args(ws),
                                 _stream_handle(stream))
     _check(rc, "gpz_field_range")
     return mm.reshape(F, 2)
@@ -447,7 +478,7 @@ def field_range_async(fields: Sequence, minmax, ws, stream=None):
     from stats_workspace."""
     F = len(fields)
     n = _check_fields(fields)
-    rc = _lib().gpz_field_range_async(ctypes.cast(_ptr_array(fields), ctypes.c_void_p), n, F,
+    rc = _lib().gpz_field_range_async(_ptr_array(fields), n, F,
                                       minmax.data_ptr(), *_ws_args(ws), _stream_handle(stream))
     _check(rc, "gpz_field_range_async")
 
@@ -458,8 +489,8 @@ def field_range_noalloc(fields: Sequence, stream=None) -> np.ndarray:
     F = len(fields)
     n = _check_fields(fields)
     mm = np.zeros(2 * F, np.float32)
-    rc = _lib().gpz_field_range_noalloc(ctypes.cast(_ptr_array(fields), ctypes.c_void_p), n, F,
-                                        mm.ctypes.data_as(ctypes.c_void_p),
+    rc = _lib().gpz_field_range_noalloc(_ptr_array(fields), n, F,
+                                        _address(mm),
                                         _stream_handle(stream))
     _check(rc, "gpz_field_range_noalloc")
     return mm.reshape(F, 2)
@@ -473,7 +504,7 @@ def rel_ebs(fields: Sequence, rel: float, stream=None, ws=None) -> np.ndarray:
     """Absolute per-field bounds for a value-range-relative bound (the field
     range kernel, then gpz_rel_to_abs per field)."""
     mm = field_range(fields, stream, ws)
-    return np.array([rel_to_abs(rel, float(a), float(b)) for a, b in mm], np.float32)
+    return np.array([rel_to_abs(rel, a, b) for a, b in mm.tolist()], np.float32)
 
 
 def inspect(prefix: bytes) -> dict:
