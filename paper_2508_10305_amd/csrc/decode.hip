@@ -45,17 +45,32 @@ union DecodeShared {
     GenDecodeSmem<64 * ITEMS> wide;
 };
 
-template <int ITEMS>
+// Words of LDS that hold a whole record in the few-blocks form (and the words
+// a staging step or an extraction may touch past its end).
+constexpr uint32_t kRecWords = 4096;
+constexpr uint32_t kRecRoom = kRecWords + 64;
+
+// WAVES > 1: the record is first copied to `recbuf` in LDS by all waves, in one
+// memory round trip for up to 4096 words, and decoded from there, wave w
+// taking fields w, w + WAVES, ... with an LDS region of its own; a longer
+// coded record is decoded by wave 0 as without.  For snapshots of few blocks, where
+// the time is one block's chain of round trips (tables, header, runs, and two
+// for every field) and of instructions, not the bytes.
+template <int ITEMS, uint32_t WAVES = 1>
 __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
-                                             DecodeShared<ITEMS>& shared) {
-    DecodeSmem<ITEMS>& sm = shared.fast;
+                                             DecodeShared<ITEMS>& shared,
+                                             DecodeShared<ITEMS>* own = nullptr,
+                                             uint32_t* recbuf = nullptr) {
+    constexpr bool WHOLE = WAVES > 1;
+    const uint32_t wave =
+        WHOLE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0u;
+    DecodeSmem<ITEMS>& sm = WHOLE ? own[wave].fast : shared.fast;
     constexpr uint32_t B = 64 * ITEMS;
     constexpr uint32_t G = ITEMS / 4;  // 16-byte groups per lane
-    uint32_t* words = sm.buf;
-    uint32_t* keys = sm.buf;
-    uint32_t* ystage = sm.buf;
+    uint32_t* const keys = sm.buf;
+    uint32_t* const ystage = sm.buf;
 
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = WHOLE ? threadIdx.x & 63u : threadIdx.x;
     const uint64_t base = (uint64_t)b * B;
     const uint32_t nb = (uint32_t)((a.n - base) < B ? (a.n - base) : B);
     const uint32_t F = a.F, K = a.K, KF = a.KF;
@@ -63,7 +78,24 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
     const uint32_t* rec;
     uint32_t len;
     if (!locate_record(a, b, lane, 0u, rec, len)) return;
-    const uint32_t h0 = len ? rec[0] : 0u;
+    bool in_lds = false;
+    if constexpr (WHOLE) {
+        // (every wave has located the same record: what follows is uniform)
+        len = readlane(len, 0);
+        in_lds = len <= kRecWords;
+        if (in_lds) {
+            constexpr uint32_t kStep = 1024;
+            for (uint32_t k = kStep * wave; k < len; k += kStep * WAVES)
+                stage_words<kStep / 64>(recbuf + k, rec + k, min(len - k, kStep), lane);
+            __syncthreads();
+        }
+    }
+    // word k of the record
+    auto word = [&](uint32_t k) -> uint32_t {
+        if constexpr (WHOLE) return (uint32_t)__builtin_amdgcn_readfirstlane((int)recbuf[k]);
+        else return rec[k];
+    };
+    const uint32_t h0 = len == 0 ? 0u : WHOLE && !in_lds ? rec[0] : word(0);
     const uint32_t mode = h0 & 3u;
 
     if (len != 0 && mode == 0 && (h0 >> 31)) {
@@ -74,7 +106,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
             if (lane == 0) *a.err = 1u;
             return;
         }
-        gen_decode_record<64 * ITEMS, 64, false>(a, b, rec, len, shared.wide);
+        gen_decode_record<64 * ITEMS, 64 * WAVES, false>(a, b, rec, len, shared.wide);
         return;
     }
     if (len == 0 || mode > 1) {
@@ -89,14 +121,22 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
         for (uint32_t f = 0; f < F; f++) {
             float* yf = a.y[f] + base;
             const uint32_t* src = rec + 1 + f * nb;
-            for (uint32_t i = lane; i < nb; i += 64) yf[i] = u2f(src[i]);
+            for (uint32_t i = 64 * wave + lane; i < nb; i += 64 * WAVES) yf[i] = u2f(src[i]);
         }
         return;
     }
 
+    if constexpr (WHOLE) {
+        // a coded record too long for the LDS, with 32-bit steps only: one wave
+        if (!in_lds) {
+            if (wave == 0) decode_block<ITEMS, 1>(a, b, shared);
+            return;
+        }
+    }
+
     // ---- coded record header
     const uint32_t U = h0 >> 2;
-    const uint32_t h1 = len > 1 ? rec[1] : 0xFFFFFFFFu;
+    const uint32_t h1 = len > 1 ? word(1) : 0xFFFFFFFFu;
     const uint32_t w_gap = h1 & 31u, w_cnt = (h1 >> 5) & 31u;
     const uint32_t s0 = (h1 >> 10) & 31u, s1 = (h1 >> 15) & 31u, s2 = (h1 >> 20) & 31u;
     bool bad = len < 2 || (h1 >> 25) != 0u || U < 1 || U > nb || w_gap > 15 || w_cnt > 12;
@@ -110,8 +150,8 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
     }
 
     // ---- undo delta + run-length coding (Sec. 4.3)
-    if (!expand_runs<ITEMS, DecodeSmem<ITEMS>::kSteps>(rec, U, w_gap, w_cnt, gw, cw, nb, K * KF,
-                                                       lane, sm.buf)) {
+    if (!expand_runs<ITEMS, WHOLE ? 0 : DecodeSmem<ITEMS>::kSteps>(
+            WHOLE ? recbuf : rec, U, w_gap, w_cnt, gw, cw, nb, K * KF, lane, sm.buf)) {
         if (lane == 0) *a.err = 1u;
         return;
     }
@@ -130,8 +170,8 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
             bad = true;
             break;
         }
-        const float lo = u2f(rec[pos]);
-        const uint32_t wn = rec[pos + 1];
+        const float lo = u2f(word((uint32_t)pos));
+        const uint32_t wn = word((uint32_t)pos + 1);
         const uint32_t w = wn & 31u, nout = wn >> 5;
         uint32_t s = 0, shift = 0;
         if (f < KF) {
@@ -144,10 +184,19 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
             bad = true;
             break;
         }
+        if (WHOLE && f % WAVES != wave) {
+            pos += 2 + pw + 2 * (uint64_t)nout;
+            continue;
+        }
         const float twoeb = 2.0f * u2f(ebt[f]);
-        wave_lds_sync();  // previous users of `words` are done
-        stage_words<DecodeSmem<ITEMS>::kSteps>(words, rec + pos + 2, pw, lane);
-        wave_lds_sync();
+        wave_lds_sync();  // previous users of the buffer are done
+        const uint32_t* words = sm.buf;
+        if constexpr (WHOLE) {
+            words = recbuf + pos + 2;
+        } else {
+            stage_words<DecodeSmem<ITEMS>::kSteps>(sm.buf, rec + pos + 2, pw, lane);
+            wave_lds_sync();
+        }
         const uint32_t mask = low_mask(w);
         uint32_t y[ITEMS];
         if (f < KF) {
@@ -174,7 +223,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
         }
         if (nout) {
             // patch outliers through LDS (the staging reuses `words`)
-            const uint32_t* ol = rec + pos + 2 + pw;
+            const uint32_t* ol = (WHOLE ? recbuf : rec) + pos + 2 + pw;
             wave_lds_sync();
 #pragma unroll
             for (int g = 0; g < G; g++)
@@ -229,6 +278,21 @@ template <int ITEMS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void decode_blocks(DecodeArgs a) {
     __shared__ __align__(16) DecodeShared<ITEMS> sm;
     decode_block<ITEMS>(a, blockIdx.x, sm);
+    post_header(a);
+}
+
+// The same for a snapshot of few blocks, at most four per CU (which is what
+// their LDS allows at B = 1024): four waves a block.  B = 1024, 6 fields, event
+// pair included: 10k particles 18.4 -> 12.6 us, 524k 18.8 -> 13.8, 1M
+// 20.5 -> 16.2 (with one wave and the record in LDS 15.3, 16.0 and 16.8);
+// above, the bytes begin to count and eight blocks per SIMD are faster.
+constexpr uint32_t kFewWaves = 4;
+
+template <int ITEMS>
+__global__ __launch_bounds__(64 * kFewWaves) void decode_few(DecodeArgs a) {
+    __shared__ __align__(16) DecodeShared<ITEMS> own[kFewWaves];
+    __shared__ __align__(16) uint32_t recbuf[kRecRoom];
+    decode_block<ITEMS, kFewWaves>(a, blockIdx.x, own[0], own, recbuf);
     post_header(a);
 }
 
@@ -313,6 +377,17 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t s) {
         return hipGetLastError();
     }
     dim3 grid(a.nblocks), block(64);
+    if (a.nblocks <= 4u * device_cu_count()) {
+        const dim3 few(64 * kFewWaves);
+        switch (a.B) {
+            case 256: hipLaunchKernelGGL(decode_few<4>, grid, few, 0, s, a); break;
+            case 512: hipLaunchKernelGGL(decode_few<8>, grid, few, 0, s, a); break;
+            case 1024: hipLaunchKernelGGL(decode_few<16>, grid, few, 0, s, a); break;
+            case 2048: hipLaunchKernelGGL(decode_few<32>, grid, few, 0, s, a); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (a.B) {
         case 256: hipLaunchKernelGGL(decode_blocks<4>, grid, block, 0, s, a); break;
         case 512: hipLaunchKernelGGL(decode_blocks<8>, grid, block, 0, s, a); break;

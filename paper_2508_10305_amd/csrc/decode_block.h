@@ -148,17 +148,20 @@ __device__ __forceinline__ bool locate_record(const DecodeArgs& a, uint32_t b, u
 // Undoes the delta and run-length coding (Sec. 4.3) of a record's segment IDs
 // (U runs, gaps then counts from rec + 2): every position's ID ends up in
 // `buf` in the padded blocked layout.  False when the IDs or the run lengths
-// do not fit the block.
+// do not fit the block.  STEPS 0: the record is in LDS already (`rec`, beside
+// `buf`).
 template <int ITEMS, int STEPS>
 __device__ __forceinline__ bool expand_runs(const uint32_t* rec, uint32_t U, uint32_t w_gap,
                                             uint32_t w_cnt, uint32_t gw, uint32_t cw, uint32_t nb,
                                             uint32_t keybits, uint32_t lane, uint32_t* buf) {
     constexpr uint32_t B = 64 * ITEMS;
     constexpr uint32_t G = ITEMS / 4;
-    uint32_t* words = buf;
+    const uint32_t* words = STEPS ? buf : rec + 2;
     uint32_t* keys = buf;
-    stage_words<STEPS>(words, rec + 2, gw + cw, lane);
-    wave_lds_sync();
+    if constexpr (STEPS > 0) {
+        stage_words<STEPS>(buf, rec + 2, gw + cw, lane);
+        wave_lds_sync();
+    }
     uint32_t g1[ITEMS], c1[ITEMS];
     uint32_t gs = 0, cs = 0;
     {
