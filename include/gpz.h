@@ -98,8 +98,9 @@ uint64_t gpz_compress_workspace_bytes(uint64_t n, uint32_t nfields, const gpz_pa
 uint64_t gpz_decompress_workspace_bytes(void);
 
 /* Compress n particles x F float32 fields (Sec. 4.1-4.4): a clearing
- * kernel, the block encoder, the length scan and the record copy
- * (GPZ_FLAG_SINGLE_PASS: clearing kernel and encoder only).
+ * kernel, the block encoder, the length scan and the record copy (up to 256
+ * blocks: the encoder and one kernel that finishes; GPZ_FLAG_SINGLE_PASS:
+ * clearing kernel and encoder only).
  *  h_fields     host array of F device pointers, each to n floats.
  *  h_eb         host array of F absolute error bounds (each in [2^-120, 2^120]).
  *  p            parameters (NULL = defaults).

@@ -262,24 +262,32 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
     ea.defer = w.defer;
     ea.defer_count = w.defer_count;
     ea.wide_flag = w.wide_flag;
+    ea.done = w.done;
+    // few blocks: two launches, nothing to clear (finish_few in generic.hip)
+    const bool few = !single && !generic && nb > 0 && nb <= kFewBlocks;
+    ea.few = few ? 1u : 0u;
+    uint32_t* const few_left = few && mail && *mail ? mail->at<uint32_t>(16) : nullptr;
 
     Timer tm(s);
-    tm.begin(kPrepare);
-    // the single pass also needs its look-back words zeroed; the three steps
-    // only the counters and superblock sums that follow them
-    int rc = to_status(
-        single ? launch_fill_u32(reinterpret_cast<uint32_t*>(w.state), 0u, w.clear_words, s)
-               : launch_fill_u32(w.ticket, 0u, w.clear_words - 2 * nb, s));
-    tm.end();
+    int rc = GPZ_OK;
+    if (!few) {
+        tm.begin(kPrepare);
+        // the single pass also needs its look-back words zeroed; the three
+        // steps only the counters and superblock sums that follow them
+        rc = to_status(
+            single ? launch_fill_u32(reinterpret_cast<uint32_t*>(w.state), 0u, w.clear_words, s)
+                   : launch_fill_u32(w.ticket, 0u, w.clear_words - 2 * nb, s));
+        tm.end();
+    }
     tm.begin(kEncode);
     if (rc == GPZ_OK)
         rc = to_status(f64 && B == 1024 ? launch_encode64(ea, s)
                        : generic        ? launch_encode_generic(ea, false, s)
                                         : launch_encode(ea, single, s));
     tm.end();
+    CopyArgs ca{};
     if (!single) {
         ScanArgs sa{};
-        CopyArgs ca{};
         for (uint32_t f = 0; f < F; f++) memcpy(&sa.eb_bits[f], &h_eb[f], 4);
         sa.supsum = w.supsum;
         sa.supoff = w.supoff;
@@ -306,16 +314,22 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
         ca.slot_words = w.slot_words;
         ca.nblocks = (uint32_t)nb;
         ca.F = F;
+        ca.left = few ? w.defer : nullptr;
         // after the wave-per-block encoder, the walk over the blocks it left
         // for 64-bit steps and the scan share one launch
         tm.begin(kScan);
         if (rc == GPZ_OK)
-            rc = to_status(generic ? launch_scan(sa, s)
-                                   : launch_encode_deferred_then_scan(ea, sa, w.done, s));
+            rc = to_status(few       ? launch_finish_few(ea, sa, ca, few_left, s)
+                           : generic ? launch_scan(sa, s)
+                                     : launch_encode_deferred_then_scan(ea, sa, w.done, s));
         tm.end();
-        tm.begin(kCopy);
-        if (rc == GPZ_OK) rc = to_status(launch_copy(ca, s));
-        tm.end();
+        // few blocks: the records are in place unless some were left; a
+        // synchronous call learns that when it waits
+        if (!few_left) {
+            tm.begin(kCopy);
+            if (rc == GPZ_OK) rc = to_status(launch_copy(ca, s));
+            tm.end();
+        }
     }
     if (sync) {
         uint64_t total = 0;
@@ -325,6 +339,12 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
         const int waited = to_status(hipStreamSynchronize(s));
         if (rc == GPZ_OK) rc = waited;
         if (*mail && rc == GPZ_OK) total = *mail->at<volatile uint64_t>();
+        if (few_left && rc == GPZ_OK && *reinterpret_cast<volatile uint32_t*>(few_left)) {
+            // some blocks took 64-bit steps: their snapshot is copied now
+            rc = to_status(launch_copy(ca, s));
+            const int copied = to_status(hipStreamSynchronize(s));
+            if (rc == GPZ_OK) rc = copied;
+        }
         if (h_out_bytes) *h_out_bytes = total;
         if (rc == GPZ_OK && total > cap) rc = GPZ_ENOSPC;
     }

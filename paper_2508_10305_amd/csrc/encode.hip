@@ -136,7 +136,9 @@ __device__ __forceinline__ void place_record(const EncodeArgs& a, uint32_t b, co
 // Leaves block b to the generic encoder (its record, length, superblock sum
 // and permutation are all written there).
 __device__ __forceinline__ void defer_block(const EncodeArgs& a, uint32_t b, uint32_t lane) {
-    if (lane == 0) a.defer[atomicAdd(a.defer_count, 1u)] = b;
+    if (lane != 0) return;
+    if (a.few) a.defer[b] = 1u;
+    else a.defer[atomicAdd(a.defer_count, 1u)] = b;
 }
 
 // The block's LDS: one region whose phases reuse it.
@@ -478,7 +480,8 @@ __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, ui
     } else if (lane == 0) {
         const uint32_t len = raw ? cap : pos;
         a.lens[b] = len;
-        atomicAdd(&a.supsum[b / kSuper], len);  // order-independent sum
+        if (a.few) a.defer[b] = 0u;
+        else atomicAdd(&a.supsum[b / kSuper], len);  // order-independent sum
     }
     if (a.perm) {
 #pragma unroll
@@ -499,6 +502,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void en
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
     const uint32_t b = blockIdx.x;
+    start_few(a, b);
     const uint64_t left = a.n - (uint64_t)b * B;
     if (left >= B) encode_block<ITEMS, true, false>(a, b, B, sm.buf);
     else encode_block<ITEMS, false, false>(a, b, (uint32_t)left, sm.buf);
@@ -521,6 +525,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<ITEMS
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
     const uint32_t b = blockIdx.x;
+    start_few(a, b);
     const uint64_t left = a.n - (uint64_t)b * B;
     if (left >= B) encode_block<ITEMS, true, false, 0>(a, b, B, sm.buf);
     else encode_block<ITEMS, false, false, 0>(a, b, (uint32_t)left, sm.buf);

@@ -11,6 +11,14 @@
 namespace gpz {
 namespace {
 
+// The few-blocks form clears for itself what the launches after it count in.
+__device__ __forceinline__ void start_few(const EncodeArgs& a, uint32_t b) {
+    if (a.few && b == 0 && threadIdx.x == 0) {
+        *a.wide_flag = 0u;
+        *a.done = 0u;
+    }
+}
+
 constexpr uint32_t kDigitBits = 5;
 constexpr uint32_t kDigits = 1u << kDigitBits;
 // Digit counters, digit-major: (d, lane) at d*68 + lane (4 pad words per

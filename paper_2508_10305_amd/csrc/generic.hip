@@ -12,6 +12,7 @@
 // ("blocked"), which is what keeps the LDS radix sort stable.  The block's
 // codes, flags, sort buffers and run tables live in LDS; every value is read
 // from global memory again where a later phase needs it.
+#include "copy_record.h"
 #include "generic_block.h"
 
 namespace gpz {
@@ -399,7 +400,7 @@ __device__ void gen_encode_block(const EncodeArgs& a, uint32_t b, GenEncodeSmem<
     if (t == 0) {
         const uint32_t len = raw ? cap : pos;
         a.lens[b] = len;
-        atomicAdd(&a.supsum[b / kSuper], len);
+        if (!a.few) atomicAdd(&a.supsum[b / kSuper], len);
         if (!raw && any_wide) atomicOr(a.wide_flag, 1u);
     }
     if (a.perm) {
@@ -464,6 +465,80 @@ __global__ __launch_bounds__(256) void gen_encode_deferred_then_scan(EncodeArgs 
     __syncthreads();
     if (!last) return;
     __threadfence();  // every other worker's writes are visible past here
+    scan_superblocks<kT>(sa, sm.part);
+}
+
+// The rest of a compression of few blocks (at most kFewBlocks) in one launch.
+// A small snapshot's time is its launches and their round trips, so nothing is
+// cleared before the encoder, no sums are kept by it, and each wave here finds
+// its record's offset from the lengths of every block (four loads a lane) and
+// copies it: a compression of 10k x 3 takes two launches instead of four,
+// 33.9 us instead of 37.6, and the step of 20k x 6 37.5 instead of 46.
+// When a block was left for 64-bit steps, the workgroups encode those blocks,
+// the last to finish scans, and the copy kernel follows.
+template <uint32_t CB>
+__global__ __launch_bounds__(256) void finish_few(EncodeArgs a, ScanArgs sa, CopyArgs ca,
+                                                  uint32_t* left_out) {
+    __shared__ __align__(16) union {
+        GenEncodeSmem<CB> enc;
+        uint64_t part[kT];
+    } sm;
+    __shared__ uint32_t last;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    constexpr uint32_t R = kFewBlocks / 64;
+    uint32_t left = 0, len[R];
+    uint64_t lefts[R];
+    uint32_t count = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < R; k++) {
+        const uint32_t i = 64 * k + lane;
+        len[k] = i < a.nblocks ? a.lens[i] : 0u;
+        left = i < a.nblocks ? a.defer[i] : 0u;
+        lefts[k] = __ballot(left != 0u);
+        count += (uint32_t)__builtin_popcountll(lefts[k]);
+    }
+    if (left_out && blockIdx.x == 0 && threadIdx.x == 0) *left_out = count ? 1u : 0u;
+    if (count == 0) {
+        const uint32_t b = blockIdx.x * 4 + wave;
+        uint64_t before = 0, total = 0;
+        uint32_t mine = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < R; k++) {
+            // (64 records of at most 2^19 words each: the sums fit 32 bits)
+            const uint32_t i = 64 * k + lane;
+            before += wave_sum_u32(i < b ? len[k] : 0u);
+            total += wave_sum_u32(len[k]);
+            mine += wave_sum_u32(i == b ? len[k] : 0u);
+        }
+        if (blockIdx.x == 0) publish_stream<kT>(sa, total);
+        if (b < a.nblocks && 4 * (sa.prefix + total) <= sa.capacity)
+            place_record(ca, b, mine, before, lane);
+        return;
+    }
+    const uint32_t workers = count < gridDim.x ? count : gridDim.x;
+    if (blockIdx.x >= workers) return;
+    uint32_t nth = 0;
+#pragma unroll 1
+    for (uint32_t b = 0; b < a.nblocks; b++) {
+        const uint64_t set = b < 64 ? lefts[0] : b < 128 ? lefts[1] : b < 192 ? lefts[2] : lefts[3];
+        if (!((set >> (b & 63u)) & 1u)) continue;
+        if (nth++ % workers != blockIdx.x) continue;
+        gen_encode_block<CB>(a, b, sm.enc);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        __threadfence();  // this workgroup's records and lengths first
+        last = atomicAdd(a.done, 1u) == workers - 1 ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();  // every other worker's writes are visible past here
+    if (wave < nsuper_of(a.nblocks)) {
+        const uint32_t i = 64 * wave + lane;
+        const uint32_t sum = wave_sum_u32(i < a.nblocks ? a.lens[i] : 0u);
+        if (lane == 0) a.supsum[wave] = sum;
+    }
+    __syncthreads();
     scan_superblocks<kT>(sa, sm.part);
 }
 
@@ -612,6 +687,14 @@ hipError_t launch_encode_deferred_then_scan(const EncodeArgs& a, const ScanArgs&
         hipLaunchKernelGGL(gen_encode_deferred_then_scan<1024>, grid, block, 0, s, a, sa, done);
     else
         hipLaunchKernelGGL(gen_encode_deferred_then_scan<2048>, grid, block, 0, s, a, sa, done);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish_few(const EncodeArgs& a, const ScanArgs& sa, const CopyArgs& ca,
+                             uint32_t* left_out, hipStream_t s) {
+    const dim3 grid((a.nblocks + 3) / 4), block(kT);
+    if (a.B <= 1024) hipLaunchKernelGGL(finish_few<1024>, grid, block, 0, s, a, sa, ca, left_out);
+    else hipLaunchKernelGGL(finish_few<2048>, grid, block, 0, s, a, sa, ca, left_out);
     return hipGetLastError();
 }
 

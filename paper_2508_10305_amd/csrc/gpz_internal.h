@@ -12,6 +12,7 @@ constexpr uint32_t kVersion = 1u;
 constexpr uint32_t kHeaderWords = 8u;
 constexpr uint32_t kSuper = 64u;          // blocks per superblock offset entry
 constexpr uint32_t kMaxFields = 64u;
+constexpr uint32_t kFewBlocks = 256;      // block count of the few-blocks encoder form, at most
 constexpr float kQMax = 16777215.0f;      // largest grid index, 2^24 - 1
 
 // ------------------------------------------------------------ stream geometry
@@ -57,6 +58,11 @@ struct EncodeArgs {
     // encoder to the generic one (three-step compaction only)
     uint32_t* defer;       // nblocks entries
     uint32_t* defer_count; // zeroed before the launch
+    // The few-blocks form (`few`, at most kFewBlocks): nothing is cleared
+    // before the launch and no sum is kept; defer[b] says whether block b is
+    // left to the generic encoder, and block 0 clears wide_flag and *done.
+    uint32_t few;
+    uint32_t* done;
     uint32_t* wide_flag;   // set when a record codes a field with 64-bit steps (zeroed before)
 };
 
@@ -88,6 +94,8 @@ struct CopyArgs {
     uint32_t slot_words;
     uint32_t nblocks;
     uint32_t F;
+    const uint32_t* left;  // few-blocks form (nullable): nonzero per block left for 64-bit steps;
+                           // with none, the records are in place already
 };
 
 struct DecodeArgs {
@@ -214,11 +222,51 @@ __device__ __forceinline__ uint32_t wave_incl_max_u32(uint32_t v) {
     return v;
 }
 
+// Whether any of the nblocks (at most kFewBlocks) entries is set, for a whole
+// wave.
+__device__ __forceinline__ bool any_left(const uint32_t* left, uint32_t nblocks) {
+    uint32_t v = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kFewBlocks / 64; k++) {
+        const uint32_t i = 64 * k + lane_id();
+        v |= i < nblocks ? left[i] : 0u;
+    }
+    return __any(v != 0u);
+}
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
+
+// Stream size of `words` record words, and, when the stream fits the output
+// buffer, its header and eb table, by T lanes.
+template <uint32_t T>
+__device__ __forceinline__ void publish_stream(const ScanArgs& a, uint64_t words) {
+    const uint32_t t = threadIdx.x;
+    const uint64_t bytes = 4 * (a.prefix + words);
+    if (t == T - 1) {
+        *a.total_bytes = bytes;
+        if (a.ext_bytes) *a.ext_bytes = bytes;
+    }
+    if (bytes <= a.capacity) {
+        if (t == 0) {
+            a.out[0] = kMagic;
+            // flags: 1 float64 fields, 2 some record has a wide field
+            const uint32_t wide = a.wide_flag && *a.wide_flag ? 2u : 0u;
+            a.out[1] = kVersion | (((a.f64 ? 1u : 0u) | wide) << 16);
+            a.out[2] = (uint32_t)(a.n & 0xFFFFFFFFu);
+            a.out[3] = (uint32_t)(a.n >> 32);
+            a.out[4] = a.F;
+            a.out[5] = a.B;
+            a.out[6] = a.K | (a.KF << 8);
+            a.out[7] = a.nblocks;
+        }
+        uint32_t* ebt = a.out + kHeaderWords + 2 * nsuper_of(a.nblocks);
+        for (uint32_t f = t; f < a.F; f += T) ebt[f] = a.eb_bits[f];
+    }
+}
 
 // Exclusive scan of the per-superblock record sizes (Sec. 4.4) by one
 // workgroup of T lanes (there are only ceil(nblocks / 64) superblocks):
@@ -248,27 +296,7 @@ __device__ __forceinline__ void scan_superblocks(const ScanArgs& a, uint64_t* pa
         a.supoff[i] = run;
         run += a.supsum[i];
     }
-    const uint64_t bytes = 4 * (a.prefix + part[T - 1]);
-    if (t == T - 1) {
-        *a.total_bytes = bytes;
-        if (a.ext_bytes) *a.ext_bytes = bytes;
-    }
-    if (bytes <= a.capacity) {
-        if (t == 0) {
-            a.out[0] = kMagic;
-            // flags: 1 float64 fields, 2 some record has a wide field
-            const uint32_t wide = a.wide_flag && *a.wide_flag ? 2u : 0u;
-            a.out[1] = kVersion | (((a.f64 ? 1u : 0u) | wide) << 16);
-            a.out[2] = (uint32_t)(a.n & 0xFFFFFFFFu);
-            a.out[3] = (uint32_t)(a.n >> 32);
-            a.out[4] = a.F;
-            a.out[5] = a.B;
-            a.out[6] = a.K | (a.KF << 8);
-            a.out[7] = a.nblocks;
-        }
-        uint32_t* ebt = a.out + kHeaderWords + 2 * nsuper_of(a.nblocks);
-        for (uint32_t f = t; f < a.F; f += T) ebt[f] = a.eb_bits[f];
-    }
+    publish_stream<T>(a, part[T - 1]);
 }
 
 // ------------------------------------------------------------ launchers
@@ -311,6 +339,11 @@ hipError_t launch_encode_generic(const EncodeArgs& a, bool deferred_only, hipStr
 // workgroup to finish its share scans; *done is zero before the launch).
 hipError_t launch_encode_deferred_then_scan(const EncodeArgs& a, const ScanArgs& sa,
                                             uint32_t* done, hipStream_t s);
+// The few-blocks form: offsets, tables, header and records in one launch when
+// no block was left to the generic encoder; else those blocks and the scan,
+// and launch_copy follows (`*left_out`, nullable, receives which: 1 or 0).
+hipError_t launch_finish_few(const EncodeArgs& a, const ScanArgs& sa, const CopyArgs& ca,
+                             uint32_t* left_out, hipStream_t s);
 hipError_t launch_decode_generic(const DecodeArgs& a, hipStream_t s);
 // The range keys as floats in device memory (min, max per field).
 hipError_t launch_range_to_floats(const int* keys, uint32_t F, float* out, hipStream_t s);
