@@ -141,6 +141,7 @@ struct CompressWs {
     uint32_t* wide_flag;    // a record codes a field with 64-bit steps
     uint32_t* done;         // workgroups of the deferred-block walk that have finished
     uint64_t clear_words;  // 32-bit words from `state` to clear before a launch
+    uint64_t* sup;         // the last look-back words, one per superblock (place.h)
     // three-step compaction
     uint32_t* lens;
     uint32_t* supsum;
@@ -177,6 +178,7 @@ CompressWs layout(uint64_t n, uint32_t F, uint32_t B, uint32_t vw, char* base) {
     w.done = ws_at<uint32_t>(base, o + nb * 8 + 24);
     w.supsum = ws_at<uint32_t>(base, o + nb * 8 + 28);
     w.clear_words = 2 * nb + 7 + ns;
+    w.sup = ws_at<uint64_t>(base, o + (nb - ns) * 8);
     o = align256(o + nb * 8 + 28 + ns * 4);
     w.supoff = ws_at<uint64_t>(base, o);
     o = align256(o + ns * 8);
@@ -266,6 +268,21 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
     // few blocks: two launches, nothing to clear (finish_few in generic.hip)
     const bool few = !single && !generic && nb > 0 && nb <= kFewBlocks;
     ea.few = few ? 1u : 0u;
+    // Large snapshots: most records are copied inside the encoder's launch
+    // (place.h); the superblock words take the look-back words' place and the
+    // flags that of the sums, cleared with the counters between them.  From
+    // four rows past the delay on (6.3M particles at B = 1024), where a
+    // quarter or more of the records are copied that way: fewer gain less
+    // than the flags and the emptier last rows cost.  A grid of 2^26
+    // workgroups or more does not fit a dispatch.
+    const bool places = !single && (!generic || (f64 && B == 1024)) &&
+                        placed_rows(nb) >= place_delay(B) + 4 &&
+                        placed_grid(nb, B) < ((uint64_t)1 << 26);
+    if (places) {
+        ea.sup = w.sup;
+        ea.supoff = w.supoff;
+        ea.copied = w.supsum;
+    }
     uint32_t* const few_left = few && mail && *mail ? mail->at<uint32_t>(16) : nullptr;
 
     Timer tm(s);
@@ -275,8 +292,10 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
         // the single pass also needs its look-back words zeroed; the three
         // steps only the counters and superblock sums that follow them
         rc = to_status(
-            single ? launch_fill_u32(reinterpret_cast<uint32_t*>(w.state), 0u, w.clear_words, s)
-                   : launch_fill_u32(w.ticket, 0u, w.clear_words - 2 * nb, s));
+            single   ? launch_fill_u32(reinterpret_cast<uint32_t*>(w.state), 0u, w.clear_words, s)
+            : places ? launch_fill_u32(reinterpret_cast<uint32_t*>(w.sup), 0u,
+                                       w.clear_words - 2 * (nb - nsuper_of(nb)), s)
+                     : launch_fill_u32(w.ticket, 0u, w.clear_words - 2 * nb, s));
         tm.end();
     }
     tm.begin(kEncode);
@@ -315,6 +334,9 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
         ca.nblocks = (uint32_t)nb;
         ca.F = F;
         ca.left = few ? w.defer : nullptr;
+        sa.sup = ea.sup;
+        ca.copied = ea.copied;
+        ca.placed = places ? (uint32_t)placed_supers(nb, B) : 0u;
         // after the wave-per-block encoder, the walk over the blocks it left
         // for 64-bit steps and the scan share one launch
         tm.begin(kScan);

@@ -45,6 +45,22 @@ __global__ __launch_bounds__(256) void copy_records(CopyArgs a) {
     copy_body(a, b, threadIdx.x & 63u);
 }
 
+// After an encoder that copied records itself (place.h): one wave per part of
+// the superblocks it was to copy, which normally finds its flag set and exits,
+// then one wave per block of the rest.
+__global__ __launch_bounds__(256) void copy_rest(CopyArgs a) {
+    constexpr uint32_t kEach = kSuper / kPlaceParts;
+    const uint32_t supers = a.placed, parts = supers * kPlaceParts;
+    const uint32_t p = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    if (p >= parts) {
+        const uint32_t b = supers * kSuper + (p - parts);
+        if (b < a.nblocks) copy_body(a, b, lane);
+        return;
+    }
+    if ((a.copied[p / kPlaceParts] >> (p % kPlaceParts)) & 1u) return;
+    for (uint32_t b = p * kEach; b < p * kEach + kEach; b++) copy_body(a, b, lane);
+}
+
 // Direct form: one wave per block of the batch's capacity (4 per
 // workgroup), as the plain copy; waves past the bound jobs' blocks exit.
 __global__ __launch_bounds__(256) void copy_records_batch_direct(const CopyArgs* jobs,
@@ -614,6 +630,11 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s) {
 
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
     if (a.nblocks == 0) return hipSuccess;
+    if (a.copied) {
+        const uint32_t waves = a.placed * kPlaceParts + (a.nblocks - a.placed * kSuper);
+        hipLaunchKernelGGL(copy_rest, dim3((waves + 3) / 4), dim3(256), 0, s, a);
+        return hipGetLastError();
+    }
     const uint32_t groups = (a.nblocks + 3) / 4;
     hipLaunchKernelGGL(copy_records, dim3(groups), dim3(256), 0, s, a);
     return hipGetLastError();

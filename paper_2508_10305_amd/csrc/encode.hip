@@ -18,6 +18,7 @@
 // partial.
 #include "encode64.h"
 #include "encode_block.h"
+#include "place.h"
 
 namespace gpz {
 namespace {
@@ -131,14 +132,6 @@ __device__ __forceinline__ void place_record(const EncodeArgs& a, uint32_t b, co
         }
     }
     if (b == a.nblocks - 1) publish_size(a, 4 * (off + len), lane);
-}
-
-// Leaves block b to the generic encoder (its record, length, superblock sum
-// and permutation are all written there).
-__device__ __forceinline__ void defer_block(const EncodeArgs& a, uint32_t b, uint32_t lane) {
-    if (lane != 0) return;
-    if (a.few) a.defer[b] = 1u;
-    else a.defer[atomicAdd(a.defer_count, 1u)] = b;
 }
 
 // The block's LDS: one region whose phases reuse it.
@@ -477,11 +470,6 @@ __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, ui
     }
     if (SINGLE) {
         place_record(a, b, rec, raw ? cap : pos, lane);
-    } else if (lane == 0) {
-        const uint32_t len = raw ? cap : pos;
-        a.lens[b] = len;
-        if (a.few) a.defer[b] = 0u;
-        else atomicAdd(&a.supsum[b / kSuper], len);  // order-independent sum
     }
     if (a.perm) {
 #pragma unroll
@@ -491,6 +479,7 @@ __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, ui
                 a.perm[base + p] = (uint32_t)(base + (raw ? p : index_of<ITEMS>(kv[j])));
         }
     }
+    if (!SINGLE) finish_block(a, b, raw ? cap : pos, lane);
 }
 
 
@@ -501,7 +490,13 @@ template <int ITEMS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void encode_blocks(EncodeArgs a) {
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
-    const uint32_t b = blockIdx.x;
+    const Role r = role_of(a, blockIdx.x);
+    if (r.idle) return;
+    if (!r.encode) {
+        place_records(a, r.super, r.part, threadIdx.x);
+        return;
+    }
+    const uint32_t b = r.block;
     start_few(a, b);
     const uint64_t left = a.n - (uint64_t)b * B;
     if (left >= B) encode_block<ITEMS, true, false>(a, b, B, sm.buf);
@@ -524,7 +519,13 @@ template <int ITEMS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<ITEMS>))) void encode_blocks_lean(EncodeArgs a) {
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
-    const uint32_t b = blockIdx.x;
+    const Role r = role_of(a, blockIdx.x);
+    if (r.idle) return;
+    if (!r.encode) {
+        place_records(a, r.super, r.part, threadIdx.x);
+        return;
+    }
+    const uint32_t b = r.block;
     start_few(a, b);
     const uint64_t left = a.n - (uint64_t)b * B;
     if (left >= B) encode_block<ITEMS, true, false, 0>(a, b, B, sm.buf);
@@ -562,9 +563,9 @@ void launch_encode_items(const EncodeArgs& a, bool single_pass, hipStream_t s) {
     // that would wait for the first)
     if (a.nblocks == 0) return;
     if constexpr (kLean<ITEMS>)
-        hipLaunchKernelGGL(encode_blocks_lean<ITEMS>, dim3(a.nblocks), dim3(64), 0, s, a);
+        hipLaunchKernelGGL(encode_blocks_lean<ITEMS>, dim3(encode_grid(a)), dim3(64), 0, s, a);
     else
-        hipLaunchKernelGGL(encode_blocks<ITEMS>, dim3(a.nblocks), dim3(64), 0, s, a);
+        hipLaunchKernelGGL(encode_blocks<ITEMS>, dim3(encode_grid(a)), dim3(64), 0, s, a);
 }
 
 // Persistent encoder over the full blocks of many snapshots: each wave takes

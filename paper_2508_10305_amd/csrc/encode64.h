@@ -20,6 +20,7 @@
 
 #include "encode_block.h"
 #include "generic_block.h"
+#include "place.h"
 
 namespace gpz {
 namespace {
@@ -480,12 +481,7 @@ __device__ __forceinline__ void encode_block64(const EncodeArgs& a, uint32_t b, 
                  ((sk[2] & 31u) << 20) | ((sk[0] >> 5) << 25) | ((sk[1] >> 5) << 26) |
                  ((sk[2] >> 5) << 27);
     }
-    if (lane == 0) {
-        const uint32_t len = raw ? cap : pos;
-        a.lens[b] = len;
-        atomicAdd(&a.supsum[b / kSuper], len);  // order-independent sum
-        if (!raw && any_wide) atomicOr(a.wide_flag, 1u);
-    }
+    if (lane == 0 && !raw && any_wide) atomicOr(a.wide_flag, 1u);
     if (a.perm) {
 #pragma unroll
         for (int j = 0; j < kItems; j++) {
@@ -494,12 +490,19 @@ __device__ __forceinline__ void encode_block64(const EncodeArgs& a, uint32_t b, 
                 a.perm[base + p] = (uint32_t)(base + (raw ? p : index_of<kItems>(kv[j])));
         }
     }
+    finish_block(a, b, raw ? cap : pos, lane);
 }
 
 // One workgroup per block; the partial last block takes the checked path.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void encode_blocks64(EncodeArgs a) {
     __shared__ __align__(16) uint32_t work[kWords64];
-    const uint32_t b = blockIdx.x;
+    const Role r = role_of(a, blockIdx.x);
+    if (r.idle) return;
+    if (!r.encode) {
+        place_records(a, r.super, r.part, threadIdx.x);
+        return;
+    }
+    const uint32_t b = r.block;
     const uint64_t left = a.n - (uint64_t)b * kB;
     if (left >= kB) encode_block64<true>(a, b, kB, work);
     else encode_block64<false>(a, b, (uint32_t)left, work);
@@ -510,7 +513,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void en
 hipError_t launch_encode64(const EncodeArgs& a, hipStream_t s) {
     if (a.B != kB) return hipErrorInvalidValue;
     if (a.nblocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(encode_blocks64, dim3(a.nblocks), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(encode_blocks64, dim3(encode_grid(a)), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

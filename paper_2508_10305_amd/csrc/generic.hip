@@ -400,7 +400,10 @@ __device__ void gen_encode_block(const EncodeArgs& a, uint32_t b, GenEncodeSmem<
     if (t == 0) {
         const uint32_t len = raw ? cap : pos;
         a.lens[b] = len;
-        if (!a.few) atomicAdd(&a.supsum[b / kSuper], len);
+        if (a.sup)
+            atomicAdd(reinterpret_cast<unsigned long long*>(a.sup + b / kSuper), (unsigned long long)len);
+        else if (!a.few)
+            atomicAdd(&a.supsum[b / kSuper], len);
         if (!raw && any_wide) atomicOr(a.wide_flag, 1u);
     }
     if (a.perm) {

@@ -29,6 +29,31 @@ __host__ __device__ inline uint32_t words_for(uint32_t count, uint32_t w) {
 }
 __host__ __device__ inline uint32_t bit_width(uint32_t v) { return v ? 32u - (uint32_t)__builtin_clz(v) : 0u; }
 
+// An encoder that also copies records into the stream (place.h): rows of one
+// superblock per XCD, all but the last place_delay of them copied by
+// kPlaceParts waves each, place_delay rows later.  placed_supers: superblocks
+// copied that way; placed_grid: the launch's workgroups.
+//
+// The delay has to cover the blocks an XCD holds at once (32 CUs: 6 rows at
+// B = 1024, 8 below, where four waves share a SIMD), or the copies wait; the
+// longer it is, the fewer records are still in the caches.  Compression alone,
+// at 8 / 9 / 10 / 12 rows: cosmology 64M x 6 489 / 503 / 509 / 512 us, LiDAR
+// 20M x 3 131 / 123 / 127 / 128; B = 512, 4M x 6 83 / 73 / 71 / 68.  With 2 or
+// 8 parts 525 and 510 (64M, 12 rows, 4 parts 512).
+constexpr uint32_t kXcds = 8;
+constexpr uint32_t kPlaceParts = 4;
+__host__ __device__ inline uint32_t place_delay(uint32_t B) { return B >= 1024 ? 8u : 12u; }
+__host__ __device__ inline uint64_t placed_rows(uint64_t nb) {
+    return (nsuper_of(nb) + kXcds - 1) / kXcds;
+}
+__host__ __device__ inline uint64_t placed_supers(uint64_t nb, uint32_t B) {
+    const uint64_t rows = placed_rows(nb), delay = place_delay(B);
+    return rows > delay ? (rows - delay) * kXcds : 0;
+}
+__host__ __device__ inline uint64_t placed_grid(uint64_t nb, uint32_t B) {
+    return placed_rows(nb) * kXcds * kSuper + placed_supers(nb, B) * kPlaceParts;
+}
+
 // ------------------------------------------------------------ kernel arguments
 
 struct EncodeArgs {
@@ -63,6 +88,11 @@ struct EncodeArgs {
     // left to the generic encoder, and block 0 clears wide_flag and *done.
     uint32_t few;
     uint32_t* done;
+    // Records copied inside the encoder's launch (place.h), when `sup` is set;
+    // it then takes supsum's place.
+    uint64_t* sup;     // a word per superblock (zeroed before)
+    uint64_t* supoff;  // a superblock's offset, once its word says it is known
+    uint32_t* copied;  // bit per part of a superblock whose records are in the stream (zeroed before)
     uint32_t* wide_flag;   // set when a record codes a field with 64-bit steps (zeroed before)
 };
 
@@ -82,6 +112,7 @@ struct ScanArgs {
     uint32_t eb_bits[kMaxFields];
     uint32_t f64;               // header flag 1: float64 fields
     const uint32_t* wide_flag;  // nonzero: header flag 2 (a record has a wide field)
+    const uint64_t* sup;        // nullable: superblock words that hold the sums instead of supsum
 };
 
 struct CopyArgs {
@@ -96,6 +127,8 @@ struct CopyArgs {
     uint32_t F;
     const uint32_t* left;  // few-blocks form (nullable): nonzero per block left for 64-bit steps;
                            // with none, the records are in place already
+    const uint32_t* copied;  // nullable: parts of the first `placed` superblocks in place already
+    uint32_t placed;
 };
 
 struct DecodeArgs {
@@ -282,7 +315,10 @@ __device__ __forceinline__ void scan_superblocks(const ScanArgs& a, uint64_t* pa
     const uint32_t lo = t * chunk;
     const uint32_t hi = lo + chunk < ns ? lo + chunk : ns;
     uint64_t sum = 0;
-    for (uint32_t i = lo; i < hi; i++) sum += a.supsum[i];
+    auto words = [&](uint32_t i) {
+        return a.sup ? (uint32_t)a.sup[i] & 0xFFFFFFFu : a.supsum[i];
+    };
+    for (uint32_t i = lo; i < hi; i++) sum += words(i);
     part[t] = sum;
     __syncthreads();
     for (uint32_t o = 1; o < T; o <<= 1) {
@@ -294,7 +330,7 @@ __device__ __forceinline__ void scan_superblocks(const ScanArgs& a, uint64_t* pa
     uint64_t run = part[t] - sum;
     for (uint32_t i = lo; i < hi; i++) {
         a.supoff[i] = run;
-        run += a.supsum[i];
+        run += words(i);
     }
     publish_stream<T>(a, part[T - 1]);
 }
