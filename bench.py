@@ -34,7 +34,7 @@ def log(*a):
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_encode_cosmology64M.md")
 ENCODER_SOURCES = ("paper_2508_10305_amd/csrc/encode.hip", "paper_2508_10305_amd/csrc/encode_block.h",
-                   "paper_2508_10305_amd/csrc/gpz_internal.h")
+                   "paper_2508_10305_amd/csrc/gpz_internal.h", "paper_2508_10305_amd/csrc/place.h")
 
 
 def encoder_source_hash() -> str:

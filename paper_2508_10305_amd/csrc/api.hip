@@ -273,11 +273,15 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
     // flags that of the sums, cleared with the counters between them.  From
     // four rows past the delay on (6.3M particles at B = 1024), where a
     // quarter or more of the records are copied that way: fewer gain less
-    // than the flags and the emptier last rows cost.  A grid of 2^26
-    // workgroups or more does not fit a dispatch.
+    // than the flags and the emptier last rows cost.  Only into a buffer that
+    // holds any stream of this shape (one that turns out too small stays as it
+    // was), and from a workspace whose superblocks share no cache line.  A grid
+    // of 2^26 workgroups or more does not fit a dispatch.
     const bool places = !single && (!generic || (f64 && B == 1024)) &&
                         placed_rows(nb) >= place_delay(B) + 4 &&
-                        placed_grid(nb, B) < ((uint64_t)1 << 26);
+                        placed_grid(nb, B) < ((uint64_t)1 << 26) &&
+                        cap >= 4 * (ea.prefix + nb + (uint64_t)F * n * vw) &&
+                        reinterpret_cast<uintptr_t>(ws) % 256 == 0;
     if (places) {
         ea.sup = w.sup;
         ea.supoff = w.supoff;

@@ -45,20 +45,25 @@ __global__ __launch_bounds__(256) void copy_records(CopyArgs a) {
     copy_body(a, b, threadIdx.x & 63u);
 }
 
-// After an encoder that copied records itself (place.h): one wave per part of
-// the superblocks it was to copy, which normally finds its flag set and exits,
-// then one wave per block of the rest.
-__global__ __launch_bounds__(256) void copy_rest(CopyArgs a) {
-    constexpr uint32_t kEach = kSuper / kPlaceParts;
-    const uint32_t supers = a.placed, parts = supers * kPlaceParts;
-    const uint32_t p = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
-    if (p >= parts) {
-        const uint32_t b = supers * kSuper + (p - parts);
+// After an encoder that copied records itself (place.h): one workgroup per
+// part of the superblocks it was to copy, which normally finds its flag set
+// and exits, then one wave per block of the rest.  Four waves a part: with
+// every block left for 64-bit steps (8M x 6 at a relative bound of 1e-8, where
+// all records are copied here) the call took 1288 us at one wave a part, 1228
+// at two, 1208 at four, 1207 at eight; cosmology 64M x 6, where nearly all
+// workgroups exit, 516.7, 518.5, 519.5, 519.6.
+constexpr uint32_t kRestWaves = 4;
+__global__ __launch_bounds__(64 * kRestWaves) void copy_rest(CopyArgs a) {
+    constexpr uint32_t kEach = kSuper / kPlaceParts, kOwn = kEach / kRestWaves;
+    const uint32_t parts = a.placed * kPlaceParts, g = blockIdx.x;
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    if (g >= parts) {
+        const uint32_t b = a.placed * kSuper + (g - parts) * kRestWaves + wave;
         if (b < a.nblocks) copy_body(a, b, lane);
         return;
     }
-    if ((a.copied[p / kPlaceParts] >> (p % kPlaceParts)) & 1u) return;
-    for (uint32_t b = p * kEach; b < p * kEach + kEach; b++) copy_body(a, b, lane);
+    if ((a.copied[g / kPlaceParts] >> (g % kPlaceParts)) & 1u) return;
+    for (uint32_t i = 0; i < kOwn; i++) copy_body(a, g * kEach + wave * kOwn + i, lane);
 }
 
 // Direct form: one wave per block of the batch's capacity (4 per
@@ -631,8 +636,9 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s) {
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
     if (a.nblocks == 0) return hipSuccess;
     if (a.copied) {
-        const uint32_t waves = a.placed * kPlaceParts + (a.nblocks - a.placed * kSuper);
-        hipLaunchKernelGGL(copy_rest, dim3((waves + 3) / 4), dim3(256), 0, s, a);
+        const uint32_t rest = a.nblocks - a.placed * kSuper;
+        hipLaunchKernelGGL(copy_rest, dim3(a.placed * kPlaceParts + (rest + kRestWaves - 1) / kRestWaves),
+                           dim3(64 * kRestWaves), 0, s, a);
         return hipGetLastError();
     }
     const uint32_t groups = (a.nblocks + 3) / 4;
