@@ -252,7 +252,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
             }
         }
         float* yf = a.y[f] + base;
-        if (full && ((reinterpret_cast<uintptr_t>(a.y[f]) & 15u) == 0)) {
+        if (full && ((reinterpret_cast<uintptr_t>(a.y[f].get()) & 15u) == 0)) {
 #pragma unroll
             for (int g = 0; g < G; g++) {
                 u32x4 t = {y[4 * g], y[4 * g + 1], y[4 * g + 2], y[4 * g + 3]};
@@ -320,9 +320,9 @@ __global__ __launch_bounds__(64) void decode_batch(const DecodeArgs* __restrict_
 
 // Direct form of decode_batch: one workgroup per block of the batch's
 // capacity (no loop around the block, so a smaller register budget).  At
-// B = 1024 seven waves per SIMD, not eight: the job's arguments, which are no
-// kernel arguments, made eight spill 68 bytes per lane (24 snapshots, 16M
-// particles x 6: 116-125 us at eight, 108 at seven, 113 at six).
+// B = 1024 seven waves per SIMD, not eight: eight leaves 63 registers and 29
+// scalars spilled into them (24 snapshots, 16M particles x 6, both
+// directions: 337 us at eight, 334 at seven).
 template <int ITEMS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ITEMS == 32 ? 3 : ITEMS == 16 ? 7 : 8))) void decode_batch_direct(const DecodeArgs* __restrict__ jobs,
                                                           const BatchLaunch* __restrict__ L) {

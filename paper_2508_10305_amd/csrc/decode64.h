@@ -48,7 +48,7 @@ __device__ __forceinline__ void decode_block64(const DecodeArgs& a, uint32_t b, 
             return;
         }
         for (uint32_t f = 0; f < F; f++) {
-            uint64_t* yf = reinterpret_cast<uint64_t*>(a.y[f]) + base;
+            uint64_t* yf = reinterpret_cast<uint64_t*>(a.y[f].get()) + base;
             const uint32_t* src = rec + 1 + 2 * f * nb;
             for (uint32_t i = lane; i < nb; i += 64)
                 yf[i] = (uint64_t)src[2 * i] | ((uint64_t)src[2 * i + 1] << 32);
@@ -147,8 +147,8 @@ __device__ __forceinline__ void decode_block64(const DecodeArgs& a, uint32_t b, 
                 y[j] = __builtin_fma((double)q, twoeb, lo);
             }
         }
-        double* yf = reinterpret_cast<double*>(a.y[f]) + base;
-        if (full && ((reinterpret_cast<uintptr_t>(a.y[f]) & 15u) == 0)) {
+        double* yf = reinterpret_cast<double*>(a.y[f].get()) + base;
+        if (full && ((reinterpret_cast<uintptr_t>(a.y[f].get()) & 15u) == 0)) {
 #pragma unroll
             for (int k = 0; k < kItems / 2; k++) {
                 const f64x2 t = {y[2 * k], y[2 * k + 1]};

@@ -260,7 +260,7 @@ __device__ __forceinline__ void encode_block64(const EncodeArgs& a, uint32_t b, 
     const uint32_t F = a.F, K = a.K, KF = a.KF;
     uint32_t* __restrict__ rec = a.temp + (uint64_t)b * a.slot_words;
     const uint32_t cap = 1 + 2 * F * nb;  // raw record length
-    auto field = [&](uint32_t f) { return reinterpret_cast<const double*>(a.x[f]); };
+    auto field = [&](uint32_t f) { return reinterpret_cast<const double*>(a.x[f].get()); };
 
     // ---- Stage 1 (Sec. 4.1): key axes, segment IDs accumulated per axis
     // (axis 0 most significant)
@@ -424,7 +424,7 @@ __device__ __forceinline__ void encode_block64(const EncodeArgs& a, uint32_t b, 
             const uint32_t cnt = __builtin_popcount(flags);
             uint32_t k = wave_incl_scan_u32(cnt) - cnt;
             uint32_t* ol = rec + pos;
-            const uint64_t* xf = reinterpret_cast<const uint64_t*>(a.x[f]) + base;
+            const uint64_t* xf = reinterpret_cast<const uint64_t*>(a.x[f].get()) + base;
 #pragma unroll 1
             for (int j = 0; j < kItems; j++) {
                 if ((flags >> j) & 1u) {
@@ -467,7 +467,7 @@ __device__ __forceinline__ void encode_block64(const EncodeArgs& a, uint32_t b, 
         __syncthreads();
         if (lane == 0) rec[0] = 1u;
         for (uint32_t f = 0; f < F; f++) {
-            const uint64_t* xf = reinterpret_cast<const uint64_t*>(a.x[f]) + base;
+            const uint64_t* xf = reinterpret_cast<const uint64_t*>(a.x[f].get()) + base;
             uint32_t* dst = rec + 1 + 2 * f * nb;
             for (uint32_t i = lane; i < nb; i += 64) {
                 const uint64_t u = xf[i];

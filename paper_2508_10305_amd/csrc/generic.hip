@@ -105,7 +105,7 @@ __device__ GenField quantize_field(const EncodeArgs& a, uint32_t f, uint64_t bas
             }
         }
     } else {
-        const double* x = reinterpret_cast<const double*>(a.x[f]) + base;
+        const double* x = reinterpret_cast<const double*>(a.x[f].get()) + base;
         double v[IPT];
         uint32_t mk = 0xFFFFFFFFu;
         bool bad = false;
@@ -356,7 +356,7 @@ __device__ void gen_encode_block(const EncodeArgs& a, uint32_t b, GenEncodeSmem<
                     const uint32_t i = cur[p];
                     ol[(1 + vw) * k] = p;
                     if (vw == 2) {
-                        const uint64_t u = d2u(reinterpret_cast<const double*>(a.x[f])[base + i]);
+                        const uint64_t u = d2u(reinterpret_cast<const double*>(a.x[f].get())[base + i]);
                         ol[(1 + vw) * k + 1] = (uint32_t)u;
                         ol[(1 + vw) * k + 2] = (uint32_t)(u >> 32);
                     } else {
@@ -380,7 +380,7 @@ __device__ void gen_encode_block(const EncodeArgs& a, uint32_t b, GenEncodeSmem<
         for (uint32_t f = 0; f < F; f++) {
             uint32_t* dst = rec + 1 + f * nb * vw;
             if (vw == 2) {
-                const uint64_t* xf = reinterpret_cast<const uint64_t*>(a.x[f]) + base;
+                const uint64_t* xf = reinterpret_cast<const uint64_t*>(a.x[f].get()) + base;
                 for (uint32_t i = t; i < nb; i += kT) {
                     const uint64_t u = xf[i];
                     dst[2 * i] = (uint32_t)u;

@@ -165,13 +165,13 @@ __device__ __forceinline__ bool eb_in_range(float eb) {
 
 __device__ __forceinline__ void put_out(const DecodeArgs& a, uint32_t f, uint64_t i, double v,
                                         bool f64) {
-    if (f64) reinterpret_cast<double*>(a.y[f])[i] = v;
+    if (f64) reinterpret_cast<double*>(a.y[f].get())[i] = v;
     else a.y[f][i] = (float)v;
 }
 
 __device__ __forceinline__ void put_raw(const DecodeArgs& a, uint32_t f, uint64_t i,
                                         const uint32_t* w, bool f64) {
-    if (f64) reinterpret_cast<uint64_t*>(a.y[f])[i] = (uint64_t)w[0] | ((uint64_t)w[1] << 32);
+    if (f64) reinterpret_cast<uint64_t*>(a.y[f].get())[i] = (uint64_t)w[0] | ((uint64_t)w[1] << 32);
     else a.y[f][i] = u2f(w[0]);
 }
 

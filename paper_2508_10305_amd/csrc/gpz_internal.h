@@ -56,8 +56,29 @@ __host__ __device__ inline uint64_t placed_grid(uint64_t nb, uint32_t B) {
 
 // ------------------------------------------------------------ kernel arguments
 
+// A pointer to device memory inside an argument block.  Read back it is a
+// global pointer also where the block lies in memory (a batch's job table):
+// there the compiler cannot tell what a loaded pointer points to and emits
+// flat accesses, which count as LDS operations too, so every wait for an LDS
+// read also waited for all loads and stores in flight (the batched encoder held
+// 192 flat loads and 322 flat stores).  24 snapshots, 16M particles x 6,
+// compression and decompression: 357 -> 333 us; kernels whose pointers are
+// kernel arguments take the same time either way.
+template <class T>
+struct Dev {
+    T* p;
+    Dev() = default;
+    __host__ __device__ Dev(T* q) : p(q) {}
+    template <class U>
+    __host__ __device__ Dev(const Dev<U>& o) : p(o.p) {}
+    __host__ __device__ T* get() const {
+        return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+    }
+    __host__ __device__ operator T*() const { return get(); }
+};
+
 struct EncodeArgs {
-    const float* x[kMaxFields];  // float32 fields, or float64 ones (f64: read as double*)
+    Dev<const float> x[kMaxFields];  // float32 fields, or float64 ones (f64: read as double*)
     float eb[kMaxFields];
     float twoeb[kMaxFields];
     float inv[kMaxFields];
@@ -65,84 +86,84 @@ struct EncodeArgs {
     uint32_t F, K, KF, B;
     uint32_t nblocks;
     uint32_t slot_words;   // record slot stride in the workspace (>= 1 + F*B)
-    uint32_t* temp;        // nblocks record slots
-    uint64_t* state;       // single pass: nblocks look-back words, zero before the launch
-    uint32_t* ticket;      // single pass: block ticket counter, zero before the launch
-    uint32_t* perm;        // nullable: n global input indices
+    Dev<uint32_t> temp;        // nblocks record slots
+    Dev<uint64_t> state;       // single pass: nblocks look-back words, zero before the launch
+    Dev<uint32_t> ticket;      // single pass: block ticket counter, zero before the launch
+    Dev<uint32_t> perm;        // nullable: n global input indices
     // three-step compaction: lengths for the scan and copy kernels
-    uint32_t* lens;        // record length (words) per block
-    uint32_t* supsum;      // per 64-block superblock: sum of record lengths (zeroed before)
+    Dev<uint32_t> lens;        // record length (words) per block
+    Dev<uint32_t> supsum;      // per 64-block superblock: sum of record lengths (zeroed before)
     // single-pass compaction: records go straight to their final offsets
-    uint32_t* out;
+    Dev<uint32_t> out;
     uint64_t capacity;     // bytes of out
     uint64_t prefix;       // words before the record area
-    uint64_t* total_bytes; // stream size, written by the last block
-    uint64_t* ext_bytes;   // nullable second destination of the size
+    Dev<uint64_t> total_bytes; // stream size, written by the last block
+    Dev<uint64_t> ext_bytes;   // nullable second destination of the size
     uint32_t f64;          // the fields are float64
     // blocks whose grid needs 64-bit steps, left by the wave-per-block
     // encoder to the generic one (three-step compaction only)
-    uint32_t* defer;       // nblocks entries
-    uint32_t* defer_count; // zeroed before the launch
+    Dev<uint32_t> defer;       // nblocks entries
+    Dev<uint32_t> defer_count; // zeroed before the launch
     // The few-blocks form (`few`, at most kFewBlocks): nothing is cleared
     // before the launch and no sum is kept; defer[b] says whether block b is
     // left to the generic encoder, and block 0 clears wide_flag and *done.
     uint32_t few;
-    uint32_t* done;
+    Dev<uint32_t> done;
     // Records copied inside the encoder's launch (place.h), when `sup` is set;
     // it then takes supsum's place.
-    uint64_t* sup;     // a word per superblock (zeroed before)
-    uint64_t* supoff;  // a superblock's offset, once its word says it is known
-    uint32_t* copied;  // bit per part of a superblock whose records are in the stream (zeroed before)
-    uint32_t* wide_flag;   // set when a record codes a field with 64-bit steps (zeroed before)
+    Dev<uint64_t> sup;     // a word per superblock (zeroed before)
+    Dev<uint64_t> supoff;  // a superblock's offset, once its word says it is known
+    Dev<uint32_t> copied;  // bit per part of a superblock whose records are in the stream (zeroed before)
+    Dev<uint32_t> wide_flag;   // set when a record codes a field with 64-bit steps (zeroed before)
 };
 
 // Three-step compaction (Sec. 4.4): scan of the superblock sums, then the copy.
 struct ScanArgs {
-    const uint32_t* supsum; // record words per superblock
-    uint64_t* supoff;       // exclusive prefix of supsum (words, inside the record area)
-    uint64_t* total_bytes;  // whole stream size in bytes
-    uint64_t* ext_bytes;    // nullable second destination of the size (async API)
+    Dev<const uint32_t> supsum; // record words per superblock
+    Dev<uint64_t> supoff;       // exclusive prefix of supsum (words, inside the record area)
+    Dev<uint64_t> total_bytes;  // whole stream size in bytes
+    Dev<uint64_t> ext_bytes;    // nullable second destination of the size (async API)
     uint32_t nsuper;
     uint64_t prefix;        // words before the record area
     // stream header, written here when the stream fits the output buffer
-    uint32_t* out;
+    Dev<uint32_t> out;
     uint64_t capacity;      // bytes
     uint64_t n;
     uint32_t F, B, K, KF, nblocks;
     uint32_t eb_bits[kMaxFields];
     uint32_t f64;               // header flag 1: float64 fields
-    const uint32_t* wide_flag;  // nonzero: header flag 2 (a record has a wide field)
-    const uint64_t* sup;        // nullable: superblock words that hold the sums instead of supsum
+    Dev<const uint32_t> wide_flag;  // nonzero: header flag 2 (a record has a wide field)
+    Dev<const uint64_t> sup;        // nullable: superblock words that hold the sums instead of supsum
 };
 
 struct CopyArgs {
-    const uint32_t* temp;
-    const uint32_t* lens;
-    const uint64_t* supoff;
-    const uint64_t* total_bytes;
-    uint32_t* out;
+    Dev<const uint32_t> temp;
+    Dev<const uint32_t> lens;
+    Dev<const uint64_t> supoff;
+    Dev<const uint64_t> total_bytes;
+    Dev<uint32_t> out;
     uint64_t capacity;     // bytes
     uint32_t slot_words;
     uint32_t nblocks;
     uint32_t F;
-    const uint32_t* left;  // few-blocks form (nullable): nonzero per block left for 64-bit steps;
+    Dev<const uint32_t> left;  // few-blocks form (nullable): nonzero per block left for 64-bit steps;
                            // with none, the records are in place already
-    const uint32_t* copied;  // nullable: parts of the first `placed` superblocks in place already
+    Dev<const uint32_t> copied;  // nullable: parts of the first `placed` superblocks in place already
     uint32_t placed;
 };
 
 struct DecodeArgs {
-    const uint32_t* in;
+    Dev<const uint32_t> in;
     uint64_t in_words;
-    float* y[kMaxFields];
+    Dev<float> y[kMaxFields];
     uint64_t n;
     uint32_t F, K, KF, B;
     uint32_t nblocks;
     uint64_t prefix;       // words before the record area
-    uint32_t* err;         // set nonzero on a malformed record
+    Dev<uint32_t> err;         // set nonzero on a malformed record
     uint32_t exact;        // in_words is the exact stream length (else an upper bound)
     uint32_t f64;          // float64 stream: y[f] are double*
-    uint32_t* header;      // nullable: receives the stream's header words
+    Dev<uint32_t> header;      // nullable: receives the stream's header words
 };
 
 // ------------------------------------------------------------ wave64 primitives
@@ -432,10 +453,10 @@ struct BatchLaunch {
     uint32_t total_blocks;  // all blocks over all jobs
     uint32_t ntail;         // jobs whose last block is partial
     uint32_t tile;          // consecutive blocks taken per work-queue grab
-    const uint32_t* full_prefix;   // njobs + 1
-    const uint32_t* block_prefix;  // njobs + 1
-    const uint32_t* tail_jobs;     // ntail job indices
-    uint32_t* counter;             // [0] encode queue head, [1] decode queue head
+    Dev<const uint32_t> full_prefix;   // njobs + 1
+    Dev<const uint32_t> block_prefix;  // njobs + 1
+    Dev<const uint32_t> tail_jobs;     // ntail job indices
+    Dev<uint32_t> counter;             // [0] encode queue head, [1] decode queue head
 };
 
 // Launch shapes of the batched kernels (fixed for the life of a batch).
