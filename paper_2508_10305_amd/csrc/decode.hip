@@ -13,6 +13,7 @@
 // flag and the block is skipped.
 #include "decode64.h"
 #include "decode_block.h"
+#include "decode_layout.h"
 
 namespace gpz {
 namespace {
@@ -45,13 +46,8 @@ union DecodeShared {
     GenDecodeSmem<64 * ITEMS> wide;
 };
 
-// Words of LDS that hold a whole record in the few-blocks form (and the words
-// a staging step or an extraction may touch past its end).
-constexpr uint32_t kRecWords = 4096;
-constexpr uint32_t kRecRoom = kRecWords + 64;
-
 // WAVES > 1: the record is first copied to `recbuf` in LDS by all waves, in one
-// memory round trip for up to 4096 words, and decoded from there, wave w
+// memory round trip for up to kFewRecWords words, and decoded from there, wave w
 // taking fields w, w + WAVES, ... with an LDS region of its own; a longer
 // coded record is decoded by wave 0 as without.  For snapshots of few blocks, where
 // the time is one block's chain of round trips (tables, header, runs, and two
@@ -82,9 +78,10 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
     if constexpr (WHOLE) {
         // (every wave has located the same record: what follows is uniform)
         len = readlane(len, 0);
-        in_lds = len <= kRecWords;
+        in_lds = len <= kFewRecWords;
         if (in_lds) {
             constexpr uint32_t kStep = 1024;
+            static_assert(kFewRecWords % kStep == 0, "whole staging steps stay inside the buffer");
             for (uint32_t k = kStep * wave; k < len; k += kStep * WAVES)
                 stage_words<kStep / 64>(recbuf + k, rec + k, min(len - k, kStep), lane);
             __syncthreads();
@@ -291,7 +288,7 @@ constexpr uint32_t kFewWaves = 4;
 template <int ITEMS>
 __global__ __launch_bounds__(64 * kFewWaves) void decode_few(DecodeArgs a) {
     __shared__ __align__(16) DecodeShared<ITEMS> own[kFewWaves];
-    __shared__ __align__(16) uint32_t recbuf[kRecRoom];
+    __shared__ __align__(16) uint32_t recbuf[few_rec_room(64 * ITEMS)];
     decode_block<ITEMS, kFewWaves>(a, blockIdx.x, own[0], own, recbuf);
     post_header(a);
 }
