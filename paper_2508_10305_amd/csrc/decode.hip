@@ -278,8 +278,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void de
     post_header(a);
 }
 
-// The same for a snapshot of few blocks, at most four per CU (which is what
-// their LDS allows at B = 1024): four waves a block.  B = 1024, 6 fields, event
+// The same for a snapshot of few blocks (few_blocks_per_cu: as many as are
+// resident at once): four waves a block.  B = 1024, 6 fields, event
 // pair included: 10k particles 18.4 -> 12.6 us, 524k 18.8 -> 13.8, 1M
 // 20.5 -> 16.2 (with one wave and the record in LDS 15.3, 16.0 and 16.8);
 // above, the bytes begin to count and eight blocks per SIMD are faster.
@@ -289,6 +289,8 @@ template <int ITEMS>
 __global__ __launch_bounds__(64 * kFewWaves) void decode_few(DecodeArgs a) {
     __shared__ __align__(16) DecodeShared<ITEMS> own[kFewWaves];
     __shared__ __align__(16) uint32_t recbuf[few_rec_room(64 * ITEMS)];
+    static_assert((sizeof(own) + sizeof(recbuf)) * few_blocks_per_cu(64 * ITEMS, 1) <= 160 * 1024,
+                  "the blocks of the form share a CU's LDS");
     decode_block<ITEMS, kFewWaves>(a, blockIdx.x, own[0], own, recbuf);
     post_header(a);
 }
@@ -374,7 +376,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t s) {
         return hipGetLastError();
     }
     dim3 grid(a.nblocks), block(64);
-    if (a.nblocks <= 4u * device_cu_count()) {
+    if (a.nblocks <= few_blocks_per_cu(a.B, a.F) * device_cu_count()) {
         const dim3 few(64 * kFewWaves);
         switch (a.B) {
             case 256: hipLaunchKernelGGL(decode_few<4>, grid, few, 0, s, a); break;

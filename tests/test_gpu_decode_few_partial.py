@@ -29,3 +29,20 @@ def test_long_record_of_a_partial_block(orc, B, part, F, eb):
     for o, r in zip(out, want):
         o = o.cpu().numpy()
         assert (o[:n].view(np.uint32) == r.view(np.uint32)).all() and o[n] == 7.0
+
+
+@pytest.mark.parametrize("blocks", [511, 512, 513])
+@pytest.mark.parametrize("F", [4, 5])
+def test_end_of_the_form_at_2048(orc, blocks, F):
+    """(two blocks per CU of a 256-CU device, up to four fields)"""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2508_10305_amd as gpz
+    rng = np.random.default_rng(blocks)
+    n = blocks * 2048 - 700
+    host = [rng.standard_normal(n).astype(np.float32) for _ in range(F)]
+    print(f"[case] B=2048 n={n} F={F}", flush=True)
+    ref, _ = orc.compress_parallel(host, 1e-2, B=2048, threads=8)
+    out = gpz.decompress(torch.from_numpy(ref).cuda(), n, F)
+    for o, r in zip(out, orc.decompress(ref, n, F)):
+        assert (o.cpu().numpy().view(np.uint32) == r.view(np.uint32)).all()
