@@ -74,9 +74,11 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
     return v;
 }
 
-// The first workgroup's copy of the stream's header for the host.
+// The first workgroup's copy of the stream's header for the host (the others
+// do not wait for the pointer's load).
 __device__ __forceinline__ void post_header(const DecodeArgs& a) {
-    if (a.header && blockIdx.x == 0 && threadIdx.x < kHeaderWords)
+    if (blockIdx.x != 0) return;
+    if (a.header && threadIdx.x < kHeaderWords)
         a.header[threadIdx.x] = a.in[threadIdx.x];
 }
 
