@@ -87,11 +87,14 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
             __syncthreads();
         }
     }
-    // word k of the record (a 64-bit index, as the record's other addresses: with
-    // a 32-bit one their reads shared no address, and the decoder of 1.3M
-    // particles x 6 took 18.9 us instead of 18.3)
+    // Word k of the record.  Through a 64-bit index, as the record's other
+    // addresses: with a 32-bit one their reads shared no address, and the decoder
+    // of 1.3M particles x 6 took 18.9 us instead of 18.3.  At B = 2048 the 32-bit
+    // index leaves 127 registers instead of 136, four waves per SIMD instead of
+    // three: 32M particles x 2 106 us instead of 124 (whole call).
     auto word = [&](uint64_t k) -> uint32_t {
         if constexpr (WHOLE) return (uint32_t)__builtin_amdgcn_readfirstlane((int)recbuf[(uint32_t)k]);
+        else if constexpr (ITEMS == 32) return rec[(uint32_t)k];
         else return rec[k];
     };
     const uint32_t h0 = len == 0 ? 0u : WHOLE && !in_lds ? rec[0] : word(0);
