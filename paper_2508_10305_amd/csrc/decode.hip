@@ -94,8 +94,8 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a, uint32_t b,
     // three: 32M particles x 2 106 us instead of 124 (whole call).
     auto word = [&](uint64_t k) -> uint32_t {
         if constexpr (WHOLE) return (uint32_t)__builtin_amdgcn_readfirstlane((int)recbuf[(uint32_t)k]);
-        else if constexpr (ITEMS == 32) return rec[(uint32_t)k];
-        else return rec[k];
+        else if constexpr (ITEMS == 32) return stream_words(rec)[(uint32_t)k];
+        else return stream_words(rec)[k];
     };
     const uint32_t h0 = len == 0 ? 0u : WHOLE && !in_lds ? rec[0] : word(0);
     const uint32_t mode = h0 & 3u;
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ITEMS == 32 
 // caller needs no host copy of the stream.
 __global__ __launch_bounds__(64) void check_empty_stream(DecodeArgs a) {
     const uint32_t lane = threadIdx.x;
-    bool bad = header_bad(a, lane);
+    bool bad = other_stream(a, 0u) || eb_table_bad(a, lane);
     if (a.exact && a.in_words != a.prefix) bad = true;
     if (__any(bad) && lane == 0) *a.err = 1u;
 }

@@ -82,33 +82,41 @@ __device__ __forceinline__ void post_header(const DecodeArgs& a) {
         a.header[threadIdx.x] = a.in[threadIdx.x];
 }
 
-// Whether the stream's header or eb table does not describe the stream the
-// caller asked for (lane k < 8 checks header word k, every lane a share of
-// the eb table).  `types`: the value-type flag asked for (0 float32, 1
-// float64).  Per-lane result.
-__device__ __forceinline__ bool header_bad(const DecodeArgs& a, uint32_t lane,
-                                           uint32_t types = 0) {
+// The stream as constant memory: no kernel writes it, and said so, a word at the
+// same index for all lanes stays a scalar load also after a store (without, every
+// word read after the one that reports a foreign header was a vector load).
+typedef const uint32_t __attribute__((address_space(4))) StreamWord;
+__device__ __forceinline__ const StreamWord* stream_words(const uint32_t* p) {
+    return (const StreamWord*)(uintptr_t)p;
+}
+
+// Whether the stream's header is not that of the stream the caller asked for.
+// `types`: the value-type flag asked for (0 float32, 1 float64); the wide-record
+// flag beside it is free.  The words are the same for every lane: scalar loads.
+__device__ __forceinline__ bool other_stream(const DecodeArgs& a, uint32_t types) {
+    const StreamWord* h = stream_words(a.in);
+    return ((h[0] ^ kMagic) | ((h[1] & ~(2u << 16)) ^ (kVersion | (types << 16))) |
+            (h[2] ^ (uint32_t)(a.n & 0xFFFFFFFFu)) | (h[3] ^ (uint32_t)(a.n >> 32)) |
+            (h[4] ^ a.F) | (h[5] ^ a.B) | (h[6] ^ (a.K | (a.KF << 8))) | (h[7] ^ a.nblocks)) != 0u;
+}
+
+// Whether the stream's eb table holds a bound out of range (every lane looks at
+// a share of it; per-lane result).
+__device__ __forceinline__ bool eb_table_bad(const DecodeArgs& a, uint32_t lane) {
     bool bad = false;
     const uint32_t* ebt = a.in + kHeaderWords + 2 * nsuper_of(a.nblocks);
     for (uint32_t f = lane; f < a.F; f += 64)
         if (!eb_ok(u2f(ebt[f]))) bad = true;
-    if (lane < kHeaderWords) {
-        const uint32_t expect[kHeaderWords] = {kMagic, kVersion, (uint32_t)(a.n & 0xFFFFFFFFu),
-                                               (uint32_t)(a.n >> 32), a.F, a.B,
-                                               a.K | (a.KF << 8), a.nblocks};
-        uint32_t want = expect[0];
-#pragma unroll
-        for (uint32_t k = 1; k < kHeaderWords; k++) want = lane == k ? expect[k] : want;
-        // word 1 may carry the wide-record flag beside the value type
-        const uint32_t got =
-            lane == 1 ? (a.in[lane] & ~(2u << 16)) ^ (types << 16) : a.in[lane];
-        if (got != want) bad = true;
-    }
     return bad;
 }
 
 // The record of block b: false (and *a.err set) when the stream's header,
-// tables or lengths are not those of the stream asked for.  The superblock
+// tables or lengths are not those of the stream asked for.  The header comes
+// first: a synchronous call starts with the decoder for the default parameters,
+// and on any other stream its blocks end there, after one round trip (block 0
+// reports it; 128M particles at B = 512: the whole call 306 us when every block
+// went through the tables and stored the flag, 286 now, 288 with the header
+// fetched before any decoder runs).  The superblock
 // entry is checked against the record area before anything is added to it,
 // and the lengths are summed in 64 bits, so no sum can wrap and every
 // accepted [rec, rec + len) lies inside the record area.
@@ -116,13 +124,18 @@ __device__ __forceinline__ bool locate_record(const DecodeArgs& a, uint32_t b, u
                                               uint32_t types, const uint32_t*& rec,
                                               uint32_t& len) {
     const uint64_t nsup = nsuper_of(a.nblocks);
-    const uint32_t* sup = a.in + kHeaderWords;
-    const uint32_t* lens = sup + 2 * nsup + a.F;
+    const StreamWord* sup = stream_words(a.in) + kHeaderWords;
+    const StreamWord* lens = sup + 2 * nsup + a.F;
     const uint64_t rec_total = a.in_words - a.prefix;
     const uint32_t sb = b / kSuper;
     const uint32_t first = sb * kSuper;
     const uint64_t sup_off = (uint64_t)sup[2 * sb] | ((uint64_t)sup[2 * sb + 1] << 32);
+    const bool other = other_stream(a, types);
     const uint64_t mine = (first + lane < b) ? (uint64_t)lens[first + lane] : 0ull;
+    if (other) {
+        if (b == 0 && lane == 0) *a.err = 1u;
+        return false;
+    }
     const uint64_t sum = sup_off + wave_sum_u64(mine);
     // every lane holds the same sum: taken from lane 0 it is a scalar, and so
     // are the record pointer and every header word read through it
@@ -132,7 +145,7 @@ __device__ __forceinline__ bool locate_record(const DecodeArgs& a, uint32_t b, u
     bool bad = sup_off > rec_total || off > rec_total || (uint64_t)len > rec_total - off;
     if (b == 0 && (sup[0] | sup[1]) != 0u) bad = true;
     if (a.exact && b + 1 == a.nblocks && off + len != rec_total) bad = true;
-    if (header_bad(a, lane, types)) bad = true;
+    if (eb_table_bad(a, lane)) bad = true;
     if (b == first && sb > 0) {
         // consistency of this superblock's offset with the previous one
         const uint64_t pl = lens[first - kSuper + lane];
