@@ -477,8 +477,11 @@ __global__ __launch_bounds__(256) void gen_encode_deferred_then_scan(EncodeArgs 
 // its record's offset from the lengths of every block (four loads a lane) and
 // copies it: a compression of 10k x 3 takes two launches instead of four,
 // 33.9 us instead of 37.6, and the step of 20k x 6 37.5 instead of 46.
-// When a block was left for 64-bit steps, the workgroups encode those blocks,
-// the last to finish scans, and the copy kernel follows.
+// When a block was left for 64-bit steps, each of those blocks has a workgroup
+// (as many are launched as there are blocks), the last to finish scans, and
+// the copy kernel follows.  256 blocks of 1024, all left, queued: 59 us with the
+// four launches, 175 with a workgroup for every four of them, one after the
+// other, 56 now.
 template <uint32_t CB>
 __global__ __launch_bounds__(256) void finish_few(EncodeArgs a, ScanArgs sa, CopyArgs ca,
                                                   uint32_t* left_out) {
@@ -489,20 +492,20 @@ __global__ __launch_bounds__(256) void finish_few(EncodeArgs a, ScanArgs sa, Cop
     __shared__ uint32_t last;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     constexpr uint32_t R = kFewBlocks / 64;
-    uint32_t left = 0, len[R];
-    uint64_t lefts[R];
-    uint32_t count = 0;
+    uint32_t len[R], count = 0;
+    uint64_t left[R];
 #pragma unroll
     for (uint32_t k = 0; k < R; k++) {
         const uint32_t i = 64 * k + lane;
         len[k] = i < a.nblocks ? a.lens[i] : 0u;
-        left = i < a.nblocks ? a.defer[i] : 0u;
-        lefts[k] = __ballot(left != 0u);
-        count += (uint32_t)__builtin_popcountll(lefts[k]);
+        const uint32_t flag = i < a.nblocks ? a.defer[i] : 0u;
+        left[k] = __ballot(flag != 0u);
+        count += (uint32_t)__builtin_popcountll(left[k]);
     }
     if (left_out && blockIdx.x == 0 && threadIdx.x == 0) *left_out = count ? 1u : 0u;
     if (count == 0) {
         const uint32_t b = blockIdx.x * 4 + wave;
+        if (blockIdx.x * 4 >= a.nblocks) return;
         uint64_t before = 0, total = 0;
         uint32_t mine = 0;
 #pragma unroll
@@ -518,20 +521,22 @@ __global__ __launch_bounds__(256) void finish_few(EncodeArgs a, ScanArgs sa, Cop
             place_record(ca, b, mine, before, lane);
         return;
     }
-    const uint32_t workers = count < gridDim.x ? count : gridDim.x;
-    if (blockIdx.x >= workers) return;
-    uint32_t nth = 0;
-#pragma unroll 1
-    for (uint32_t b = 0; b < a.nblocks; b++) {
-        const uint64_t set = b < 64 ? lefts[0] : b < 128 ? lefts[1] : b < 192 ? lefts[2] : lefts[3];
-        if (!((set >> (b & 63u)) & 1u)) continue;
-        if (nth++ % workers != blockIdx.x) continue;
-        gen_encode_block<CB>(a, b, sm.enc);
-        __syncthreads();
+    if (blockIdx.x >= count) return;
+    // the left block of this workgroup's number
+    uint32_t own = 0, before = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < R; k++) {
+        const uint32_t rank =
+            before + (uint32_t)__builtin_popcountll(left[k] & ((1ull << lane) - 1ull));
+        const uint64_t mine = __ballot(((left[k] >> lane) & 1u) && rank == blockIdx.x);
+        if (mine) own = 64 * k + (uint32_t)__builtin_ctzll(mine);
+        before += (uint32_t)__builtin_popcountll(left[k]);
     }
+    gen_encode_block<CB>(a, own, sm.enc);
+    __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();  // this workgroup's records and lengths first
-        last = atomicAdd(a.done, 1u) == workers - 1 ? 1u : 0u;
+        last = atomicAdd(a.done, 1u) == count - 1 ? 1u : 0u;
     }
     __syncthreads();
     if (!last) return;
@@ -695,7 +700,7 @@ hipError_t launch_encode_deferred_then_scan(const EncodeArgs& a, const ScanArgs&
 
 hipError_t launch_finish_few(const EncodeArgs& a, const ScanArgs& sa, const CopyArgs& ca,
                              uint32_t* left_out, hipStream_t s) {
-    const dim3 grid((a.nblocks + 3) / 4), block(kT);
+    const dim3 grid(a.nblocks), block(kT);
     if (a.B <= 1024) hipLaunchKernelGGL(finish_few<1024>, grid, block, 0, s, a, sa, ca, left_out);
     else hipLaunchKernelGGL(finish_few<2048>, grid, block, 0, s, a, sa, ca, left_out);
     return hipGetLastError();
