@@ -38,10 +38,11 @@ __device__ __forceinline__ void copy_body(const CopyArgs& a, uint32_t b, uint32_
     place_record(a, b, a.lens[b], a.supoff[sb] + before, lane);
 }
 
+template <bool FEW>
 __global__ __launch_bounds__(256) void copy_records(CopyArgs a) {
     const uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= a.nblocks) return;
-    if (a.left && !any_left(a.left, a.nblocks)) return;  // finish_few placed the records
+    if (FEW && !any_left(a.left, a.nblocks)) return;  // finish_few placed the records
     copy_body(a, b, threadIdx.x & 63u);
 }
 
@@ -647,7 +648,8 @@ hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
         return hipGetLastError();
     }
     const uint32_t groups = (a.nblocks + 3) / 4;
-    hipLaunchKernelGGL(copy_records, dim3(groups), dim3(256), 0, s, a);
+    if (a.left) hipLaunchKernelGGL(copy_records<true>, dim3(groups), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(copy_records<false>, dim3(groups), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -159,7 +159,7 @@ struct EncodeSmem {
 // EARLY: how many fields after the key fields are loaded and quantized with
 // them, before the sort (at most three); the others are loaded and quantized
 // in the field loop.  With none, fewer values are held across the sort.
-template <int ITEMS, bool FULL, bool SINGLE, int EARLY = 3>
+template <int ITEMS, bool FULL, bool SINGLE, int EARLY = 3, int FORM = kPlain>
 __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, uint32_t nb,
                                              uint32_t* work) {
     uint32_t* const stage = work + EncodeSmem<ITEMS>::kStageAt;
@@ -221,7 +221,7 @@ __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, ui
     // for it, stores the block raw.
     bool wide = ck[0].wide || ck[1].wide || ck[2].wide || co[0].wide || co[1].wide || co[2].wide;
     if (!SINGLE && wide) {
-        defer_block(a, b, lane);
+        defer_block<FORM>(a, b, lane);
         return;
     }
 
@@ -453,7 +453,7 @@ __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, ui
     }
 
     if (!SINGLE && wide) {
-        defer_block(a, b, lane);
+        defer_block<FORM>(a, b, lane);
         return;
     }
     const bool raw = over || pos >= cap;
@@ -479,28 +479,31 @@ __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, ui
                 a.perm[base + p] = (uint32_t)(base + (raw ? p : index_of<ITEMS>(kv[j])));
         }
     }
-    if (!SINGLE) finish_block(a, b, raw ? cap : pos, lane);
+    if (!SINGLE) finish_block<FORM>(a, b, raw ? cap : pos, lane);
 }
 
 
 // Three-step compaction: one workgroup per block, block index = workgroup
 // index.  Full blocks take the path without bounds checks, the partial last
 // block (if any) the checked one.
-template <int ITEMS>
+template <int ITEMS, int FORM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void encode_blocks(EncodeArgs a) {
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
-    const Role r = role_of(a, blockIdx.x);
-    if (r.idle) return;
-    if (!r.encode) {
-        place_records(a, r.super, r.part, threadIdx.x);
-        return;
+    uint32_t b = blockIdx.x;
+    if constexpr (FORM == kPlaces) {
+        const Role r = role_of(a, b);
+        if (r.idle) return;
+        if (!r.encode) {
+            place_records(a, r.super, r.part, threadIdx.x);
+            return;
+        }
+        b = r.block;
     }
-    const uint32_t b = r.block;
-    start_few(a, b);
+    if constexpr (FORM == kFew) start_few(a, b);
     const uint64_t left = a.n - (uint64_t)b * B;
-    if (left >= B) encode_block<ITEMS, true, false>(a, b, B, sm.buf);
-    else encode_block<ITEMS, false, false>(a, b, (uint32_t)left, sm.buf);
+    if (left >= B) encode_block<ITEMS, true, false, 3, FORM>(a, b, B, sm.buf);
+    else encode_block<ITEMS, false, false, 3, FORM>(a, b, (uint32_t)left, sm.buf);
 }
 
 // The same with no early fields beside the key fields (EARLY = 0) and the
@@ -515,21 +518,24 @@ constexpr bool kLean = ITEMS <= 16;
 template <int ITEMS>
 constexpr int kWaves = ITEMS == 16 ? 3 : ITEMS < 16 ? 4 : 2;
 
-template <int ITEMS>
+template <int ITEMS, int FORM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<ITEMS>))) void encode_blocks_lean(EncodeArgs a) {
     constexpr uint32_t B = 64 * ITEMS;
     __shared__ EncodeSmem<ITEMS> sm;
-    const Role r = role_of(a, blockIdx.x);
-    if (r.idle) return;
-    if (!r.encode) {
-        place_records(a, r.super, r.part, threadIdx.x);
-        return;
+    uint32_t b = blockIdx.x;
+    if constexpr (FORM == kPlaces) {
+        const Role r = role_of(a, b);
+        if (r.idle) return;
+        if (!r.encode) {
+            place_records(a, r.super, r.part, threadIdx.x);
+            return;
+        }
+        b = r.block;
     }
-    const uint32_t b = r.block;
-    start_few(a, b);
+    if constexpr (FORM == kFew) start_few(a, b);
     const uint64_t left = a.n - (uint64_t)b * B;
-    if (left >= B) encode_block<ITEMS, true, false, 0>(a, b, B, sm.buf);
-    else encode_block<ITEMS, false, false, 0>(a, b, (uint32_t)left, sm.buf);
+    if (left >= B) encode_block<ITEMS, true, false, 0, FORM>(a, b, B, sm.buf);
+    else encode_block<ITEMS, false, false, 0, FORM>(a, b, (uint32_t)left, sm.buf);
 }
 
 // Single-pass compaction: blocks are numbered by a ticket taken when the
@@ -562,10 +568,16 @@ void launch_encode_items(const EncodeArgs& a, bool single_pass, hipStream_t s) {
     // last block the checked one, alongside them (not in a second launch
     // that would wait for the first)
     if (a.nblocks == 0) return;
-    if constexpr (kLean<ITEMS>)
-        hipLaunchKernelGGL(encode_blocks_lean<ITEMS>, dim3(encode_grid(a)), dim3(64), 0, s, a);
-    else
-        hipLaunchKernelGGL(encode_blocks<ITEMS>, dim3(encode_grid(a)), dim3(64), 0, s, a);
+    const dim3 grid(encode_grid(a)), block(64);
+    if constexpr (kLean<ITEMS>) {
+        if (a.sup) hipLaunchKernelGGL((encode_blocks_lean<ITEMS, kPlaces>), grid, block, 0, s, a);
+        else if (a.few) hipLaunchKernelGGL((encode_blocks_lean<ITEMS, kFew>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((encode_blocks_lean<ITEMS, kPlain>), grid, block, 0, s, a);
+    } else {
+        if (a.sup) hipLaunchKernelGGL((encode_blocks<ITEMS, kPlaces>), grid, block, 0, s, a);
+        else if (a.few) hipLaunchKernelGGL((encode_blocks<ITEMS, kFew>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((encode_blocks<ITEMS, kPlain>), grid, block, 0, s, a);
+    }
 }
 
 // Persistent encoder over the full blocks of many snapshots: each wave takes

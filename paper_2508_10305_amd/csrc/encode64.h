@@ -490,7 +490,7 @@ __device__ __forceinline__ void encode_block64(const EncodeArgs& a, uint32_t b, 
                 a.perm[base + p] = (uint32_t)(base + (raw ? p : index_of<kItems>(kv[j])));
         }
     }
-    finish_block(a, b, raw ? cap : pos, lane);
+    finish_block<kPlaces>(a, b, raw ? cap : pos, lane);
 }
 
 // One workgroup per block; the partial last block takes the checked path.

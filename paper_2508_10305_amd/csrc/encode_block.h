@@ -13,7 +13,7 @@ namespace {
 
 // The few-blocks form clears for itself what the launches after it count in.
 __device__ __forceinline__ void start_few(const EncodeArgs& a, uint32_t b) {
-    if (a.few && b == 0 && threadIdx.x == 0) {
+    if (b == 0 && threadIdx.x == 0) {
         *a.wide_flag = 0u;
         *a.done = 0u;
     }

@@ -59,10 +59,18 @@ __device__ __forceinline__ uint32_t xcd_id() {
 // Every store of this wave has reached its L2.
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// The encoder's forms: the plain one, the few-blocks one, and the one whose
+// launch also copies records (when a.sup is set).  Each is a kernel of its own:
+// with one that looks at the arguments, a compression of 262k x 2 at B = 512
+// took 23.1 us (22.5 plain, with the launches around it), 2.9M x 2 50.2 (49.5),
+// 1M x 2 at B = 1024 26.8 (26.1).
+enum Form : int { kPlain = 0, kFew = 1, kPlaces = 2 };
+
 // Block b's record (len words) is in its slot.
+template <int FORM>
 __device__ __forceinline__ void finish_block(const EncodeArgs& a, uint32_t b, uint32_t len,
                                              uint32_t lane) {
-    if (a.sup) {
+    if (FORM == kPlaces && a.sup) {
         if (lane == 0) a.lens[b] = len;
         wait_stores();
         if (lane == 0) {
@@ -74,21 +82,22 @@ __device__ __forceinline__ void finish_block(const EncodeArgs& a, uint32_t b, ui
         }
     } else if (lane == 0) {
         a.lens[b] = len;
-        if (a.few) a.defer[b] = 0u;
+        if (FORM == kFew) a.defer[b] = 0u;
         else atomicAdd(&a.supsum[b / kSuper], len);  // order-independent sum
     }
 }
 
 // Leaves block b to the generic encoder (its record, length, superblock sum
 // and permutation are all written there).
+template <int FORM>
 __device__ __forceinline__ void defer_block(const EncodeArgs& a, uint32_t b, uint32_t lane) {
     if (lane != 0) return;
-    if (a.few) {
+    if (FORM == kFew) {
         a.defer[b] = 1u;
         return;
     }
     a.defer[atomicAdd(a.defer_count, 1u)] = b;
-    if (a.sup)
+    if (FORM == kPlaces && a.sup)
         __hip_atomic_fetch_or(a.sup + b / kSuper, kSupLeft, __ATOMIC_RELAXED,
                               __HIP_MEMORY_SCOPE_AGENT);
 }
