@@ -202,7 +202,7 @@ __device__ __forceinline__ void check_load(const float* p, bool whole, uint32_t 
 // separate range pass another 100.
 template <bool STATS>
 __global__ __launch_bounds__(64 * kCheckWaves) __attribute__((amdgpu_waves_per_eu(4))) void bound_check_kernel(BoundArgs a) {
-    __shared__ float win[kCheckWaves][kCheckChunk];
+    __shared__ __align__(16) float win[kCheckWaves][kCheckChunk];  // stored 16 bytes at a time
     __shared__ double sm[kCheckWaves][kMaxFields], ss[kCheckWaves][kMaxFields];
     __shared__ unsigned long long sv[kCheckWaves][kMaxFields];
     __shared__ int skn[kCheckWaves][kMaxFields], skx[kCheckWaves][kMaxFields];

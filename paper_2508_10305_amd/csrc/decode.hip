@@ -294,6 +294,7 @@ template <int ITEMS>
 __global__ __launch_bounds__(64 * kFewWaves) void decode_few(DecodeArgs a) {
     __shared__ __align__(16) DecodeShared<ITEMS> own[kFewWaves];
     __shared__ __align__(16) uint32_t recbuf[few_rec_room(64 * ITEMS)];
+    static_assert(sizeof(own[0]) % 16 == 0, "every wave's region is stored 16 bytes at a time");
     static_assert((sizeof(own) + sizeof(recbuf)) * few_blocks_per_cu(64 * ITEMS, 1) <= 160 * 1024,
                   "the blocks of the form share a CU's LDS");
     decode_block<ITEMS, kFewWaves>(a, blockIdx.x, own[0], own, recbuf);
