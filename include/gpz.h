@@ -94,6 +94,14 @@ uint64_t gpz_max_compressed_bytes(uint64_t n, uint32_t nfields, const gpz_params
  * bytes.  Returns 0 for invalid parameters. */
 uint64_t gpz_compress_workspace_bytes(uint64_t n, uint32_t nfields, const gpz_params *p);
 
+/* Memory of the synchronous calls (gpz_compress, gpz_decompress, their float64
+ * forms and the reporting calls; the _async and _noalloc calls use none of
+ * this).  Given a workspace they allocate no device memory.  Each borrows, until
+ * it returns, a page of 4 KB of pinned host memory that its kernels write their
+ * small results to.  The process makes a page when a call finds none free, at
+ * most 64, and keeps them; a call that gets none works as well, through
+ * a copy of its own. */
+
 /* Device workspace gpz_decompress needs (an error flag). */
 uint64_t gpz_decompress_workspace_bytes(void);
 
@@ -171,10 +179,8 @@ int gpz_decompress_async(const void *d_in, uint64_t in_bytes, float *const *h_fi
 /* Device workspace of the reporting calls below (gpz_bound_check,
  * gpz_error_stats, gpz_stream_stats, gpz_field_range): 32 bytes per field
  * plus 64, rounded up to 256.  0 for F outside 1..64.  With a workspace these
- * calls allocate no device memory (a synchronous call may borrow one of at
- * most 64 pages of 4 KB of pinned host memory that the process makes as calls
- * overlap; none, and all calls work as before); with d_ws == NULL the library allocates and frees
- * one per call (GPZ_ENOMEM if it cannot).  A workspace may be reused by
+ * calls allocate no device memory; with d_ws == NULL the library allocates and
+ * frees one per call (GPZ_ENOMEM if it cannot).  A workspace may be reused by
  * calls that run one after the other on one stream, not by concurrent ones. */
 uint64_t gpz_stats_workspace_bytes(uint32_t nfields);
 
@@ -205,7 +211,7 @@ typedef struct {
  * every field, its sum of squared errors and normalized RMSE over the
  * original field's value range (h_out[F]), and the aggregate PSNR
  * -20 log10 sqrt(mean over fields of NRMSE^2) in dB (*h_psnr, nullable).
- * Reads orig twice (errors, then its range).  Synchronizes `stream`. */
+ * Synchronizes `stream`. */
 int gpz_error_stats(const float *const *h_orig, const float *const *h_recon,
                     const uint32_t *d_perm, uint64_t n, uint32_t nfields, const float *h_eb,
                     gpz_field_error *h_out, double *h_psnr, void *d_ws, uint64_t ws_bytes,

@@ -65,7 +65,7 @@ struct Timer {
 constexpr size_t kMailboxBytes = 4096;
 constexpr int kMailboxes = 64;
 std::mutex g_mail_mu;
-char* g_mail_free[kMailboxes];  // those not borrowed; never released to the system
+char* g_mail_free[kMailboxes];  // those not borrowed; kept for the life of the process
 int g_mail_nfree = 0, g_mail_made = 0;
 bool alloc_fault();
 
@@ -74,12 +74,16 @@ class Mailbox {
 
   public:
     Mailbox() {
-        std::lock_guard<std::mutex> lock(g_mail_mu);
-        if (g_mail_nfree > 0) {
-            p_ = g_mail_free[--g_mail_nfree];
-            return;
+        {
+            std::lock_guard<std::mutex> lock(g_mail_mu);
+            if (g_mail_nfree > 0) {
+                p_ = g_mail_free[--g_mail_nfree];
+                return;
+            }
+            if (g_mail_made >= kMailboxes || alloc_fault()) return;
+            g_mail_made++;
         }
-        if (g_mail_made >= kMailboxes || alloc_fault()) return;
+        // Made without the lock: other threads' calls go on meanwhile.
         // (another thread may be capturing a graph: an allocation must not
         // invalidate its capture)
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -88,11 +92,14 @@ class Mailbox {
         if (hipHostMalloc(&p, kMailboxBytes, hipHostMallocPortable | hipHostMallocMapped) ==
             hipSuccess) {
             p_ = static_cast<char*>(p);
-            g_mail_made++;
         } else {
             (void)hipGetLastError();
         }
         (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!p_) {
+            std::lock_guard<std::mutex> lock(g_mail_mu);
+            g_mail_made--;
+        }
     }
     ~Mailbox() {
         if (!p_) return;
