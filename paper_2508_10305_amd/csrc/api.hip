@@ -312,7 +312,7 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
     tm.begin(kEncode);
     if (rc == GPZ_OK)
         rc = to_status(f64 && B == 1024 ? launch_encode64(ea, s)
-                       : generic        ? launch_encode_generic(ea, false, s)
+                       : generic        ? launch_encode_generic(ea, s)
                                         : launch_encode(ea, single, s));
     tm.end();
     CopyArgs ca{};

@@ -403,4 +403,11 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_decode64(const DecodeArgs& a, hipStream_t s) {
+    if (a.B != 1024u) return hipErrorInvalidValue;
+    if (a.nblocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(decode_blocks64, dim3(a.nblocks), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
 }  // namespace gpz

@@ -195,12 +195,4 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void de
 }
 
 }  // namespace
-
-hipError_t launch_decode64(const DecodeArgs& a, hipStream_t s) {
-    if (a.B != kB) return hipErrorInvalidValue;
-    if (a.nblocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(decode_blocks64, dim3(a.nblocks), dim3(64), 0, s, a);
-    return hipGetLastError();
-}
-
 }  // namespace gpz

@@ -688,4 +688,11 @@ hipError_t launch_encode(const EncodeArgs& a, bool single_pass, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_encode64(const EncodeArgs& a, hipStream_t s) {
+    if (a.B != 1024u) return hipErrorInvalidValue;
+    if (a.nblocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(encode_blocks64, dim3(encode_grid(a)), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
 }  // namespace gpz

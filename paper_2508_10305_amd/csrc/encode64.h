@@ -509,12 +509,4 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void en
 }
 
 }  // namespace
-
-hipError_t launch_encode64(const EncodeArgs& a, hipStream_t s) {
-    if (a.B != kB) return hipErrorInvalidValue;
-    if (a.nblocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(encode_blocks64, dim3(encode_grid(a)), dim3(64), 0, s, a);
-    return hipGetLastError();
-}
-
 }  // namespace gpz

@@ -422,21 +422,9 @@ __global__ __launch_bounds__(256) void gen_encode_all(EncodeArgs a) {
     gen_encode_block<CB>(a, blockIdx.x, sm);
 }
 
-// The blocks the fast encoder left on the deferred list (their grid needs
-// 64-bit steps); a fixed grid walks the list, whose length is only known on
-// the device.
-template <uint32_t CB>
-__global__ __launch_bounds__(256) void gen_encode_deferred(EncodeArgs a) {
-    __shared__ __align__(16) GenEncodeSmem<CB> sm;
-    const uint32_t count = *a.defer_count;
-    for (uint32_t k = blockIdx.x; k < count; k += gridDim.x) {
-        gen_encode_block<CB>(a, a.defer[k], sm);
-        __syncthreads();
-    }
-}
-
-// The deferred blocks, then the length scan (second compaction step,
-// Sec. 4.4) in the same launch.  Workgroup g < min(count, grid) walks its
+// The blocks the wave-per-block encoder left on its list (their grid needs
+// 64-bit steps; the list's length is only known on the device), then the
+// length scan (second compaction step, Sec. 4.4) in the same launch.  Workgroup g < min(count, grid) walks its
 // share of the list; the last of those to finish (counted in *done) scans
 // the superblock sums, which by then hold every block's length.  With no
 // deferred block, workgroup 0 scans at once and no counter is touched (an
@@ -668,19 +656,12 @@ uint32_t walk_grid(uint32_t nblocks) {
 
 }  // namespace
 
-hipError_t launch_encode_generic(const EncodeArgs& a, bool deferred_only, hipStream_t s) {
+hipError_t launch_encode_generic(const EncodeArgs& a, hipStream_t s) {
     if (a.nblocks == 0) return hipSuccess;
-    const dim3 block(kT);
-    if (deferred_only) {
-        const dim3 grid(walk_grid(a.nblocks));
-        if (a.B <= 1024) hipLaunchKernelGGL(gen_encode_deferred<1024>, grid, block, 0, s, a);
-        else hipLaunchKernelGGL(gen_encode_deferred<4096>, grid, block, 0, s, a);
-    } else {
-        const dim3 grid(a.nblocks);
-        if (a.B <= 256) hipLaunchKernelGGL(gen_encode_all<256>, grid, block, 0, s, a);
-        else if (a.B <= 1024) hipLaunchKernelGGL(gen_encode_all<1024>, grid, block, 0, s, a);
-        else hipLaunchKernelGGL(gen_encode_all<4096>, grid, block, 0, s, a);
-    }
+    const dim3 grid(a.nblocks), block(kT);
+    if (a.B <= 256) hipLaunchKernelGGL(gen_encode_all<256>, grid, block, 0, s, a);
+    else if (a.B <= 1024) hipLaunchKernelGGL(gen_encode_all<1024>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(gen_encode_all<4096>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -689,8 +670,8 @@ hipError_t launch_encode_deferred_then_scan(const EncodeArgs& a, const ScanArgs&
     // two workgroups per CU: few empty workgroups when nothing is deferred
     const uint32_t g = 2u * device_cu_count();
     const dim3 grid(a.nblocks < g ? (a.nblocks ? a.nblocks : 1u) : g), block(kT);
-    // (the wave-per-block encoder's blocks hold at most 2048 particles; with
-    // the 57 KB of LDS of 4096 an empty walk took 30 us, with 2048's 29)
+    // (the wave-per-block encoder's blocks hold at most 2048 particles: with the
+    // 57 KB of LDS of 4096 an empty walk took 30 us, with the 29 KB of 2048 7 us)
     if (a.B <= 1024)
         hipLaunchKernelGGL(gen_encode_deferred_then_scan<1024>, grid, block, 0, s, a, sa, done);
     else

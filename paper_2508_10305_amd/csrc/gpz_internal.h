@@ -387,11 +387,8 @@ hipError_t launch_stream_stats(const uint32_t* in, uint64_t in_words, uint64_t n
 hipError_t launch_field_range(const float* const* x, uint64_t n, uint32_t F, int* keys,
                               hipStream_t s);
 // Generic 256-lane-per-block kernels (float64 fields, fields needing 64-bit
-// grid steps, any block size).  deferred_only: the blocks the wave-per-block
-// encoder left on its list; otherwise every block.  The decoder takes every
-// block (the wave-per-block decoder decodes records with a wide field
-// itself).
-hipError_t launch_encode_generic(const EncodeArgs& a, bool deferred_only, hipStream_t s);
+// grid steps, any block size), every block of a snapshot or stream.
+hipError_t launch_encode_generic(const EncodeArgs& a, hipStream_t s);
 // The deferred blocks, then the length scan in the same launch (the last
 // workgroup to finish its share scans; *done is zero before the launch).
 hipError_t launch_encode_deferred_then_scan(const EncodeArgs& a, const ScanArgs& sa,
