@@ -278,13 +278,20 @@ int compress_impl(const void* const* h_fields, bool f64, uint64_t n, uint32_t F,
     // Large snapshots: most records are copied inside the encoder's launch
     // (place.h); the superblock words take the look-back words' place and the
     // flags that of the sums, cleared with the counters between them.  From
-    // four rows past the delay on (6.3M particles at B = 1024), where a
-    // quarter or more of the records are copied that way: fewer gain less
-    // than the flags and the emptier last rows cost.  Only into a buffer that
-    // holds any stream of this shape (one that turns out too small stays as it
-    // was), and from a workspace whose superblocks share no cache line.  A grid
-    // of 2^26 workgroups or more does not fit a dispatch.
-    const bool places = !single && (!generic || (f64 && B == 1024)) &&
+    // four rows past the delay on (more than 5.77M particles at B = 1024): there a
+    // call gains 5 to 9 % (B = 1024 x 2 fields 56.0 -> 53.2 us, x 6 92.0 -> 86.6;
+    // float64 x 3 109.8 -> 104.3; B = 512, 4.2M x 6 80.7 -> 75.5; B = 256, 2.1M x 6
+    // 65.8 -> 61.9).
+    // From one row on, a call alone gained as much (4.7M x 6 79.9 -> 75.4), but two
+    // on two streams, which overlap one's copies with the other's encoder, lost
+    // (108.9 -> 121.0); above the line such a pair takes between 5 % less and 6 %
+    // more (x 6, in us: 6.3M 190 -> 180, 8M 180 -> 191, 16M 325 -> 339, 32M 663 -> 633),
+    // and a snapshot whose first block is left for 64-bit steps, so that nothing
+    // can be copied early, 0 to 4 % more.  Not at B = 2048 (place_delay).
+    // Only into a buffer that holds any stream of this shape (one that turns out
+    // too small stays as it was), and from a workspace whose superblocks share no
+    // cache line.  A grid of 2^26 workgroups or more does not fit a dispatch.
+    const bool places = !single && B <= 1024 && (!generic || (f64 && B == 1024)) &&
                         placed_rows(nb) >= place_delay(B) + 4 &&
                         placed_grid(nb, B) < ((uint64_t)1 << 26) &&
                         cap >= 4 * (ea.prefix + nb + (uint64_t)F * n * vw) &&

@@ -489,17 +489,9 @@ __device__ __forceinline__ void encode_block(const EncodeArgs& a, uint32_t b, ui
 template <int ITEMS, int FORM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void encode_blocks(EncodeArgs a) {
     constexpr uint32_t B = 64 * ITEMS;
+    static_assert(FORM != kPlaces, "the lean form copies records");
     __shared__ EncodeSmem<ITEMS> sm;
-    uint32_t b = blockIdx.x;
-    if constexpr (FORM == kPlaces) {
-        const Role r = role_of(a, b);
-        if (r.idle) return;
-        if (!r.encode) {
-            place_records(a, r.super, r.part, threadIdx.x);
-            return;
-        }
-        b = r.block;
-    }
+    const uint32_t b = blockIdx.x;
     if constexpr (FORM == kFew) start_few(a, b);
     const uint64_t left = a.n - (uint64_t)b * B;
     if (left >= B) encode_block<ITEMS, true, false, 3, FORM>(a, b, B, sm.buf);
@@ -574,8 +566,7 @@ void launch_encode_items(const EncodeArgs& a, bool single_pass, hipStream_t s) {
         else if (a.few) hipLaunchKernelGGL((encode_blocks_lean<ITEMS, kFew>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((encode_blocks_lean<ITEMS, kPlain>), grid, block, 0, s, a);
     } else {
-        if (a.sup) hipLaunchKernelGGL((encode_blocks<ITEMS, kPlaces>), grid, block, 0, s, a);
-        else if (a.few) hipLaunchKernelGGL((encode_blocks<ITEMS, kFew>), grid, block, 0, s, a);
+        if (a.few) hipLaunchKernelGGL((encode_blocks<ITEMS, kFew>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((encode_blocks<ITEMS, kPlain>), grid, block, 0, s, a);
     }
 }

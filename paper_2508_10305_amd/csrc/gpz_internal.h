@@ -35,14 +35,21 @@ __host__ __device__ inline uint32_t bit_width(uint32_t v) { return v ? 32u - (ui
 // copied that way; placed_grid: the launch's workgroups.
 //
 // The delay has to cover the blocks an XCD holds at once (32 CUs: 6 rows at
-// B = 1024, 8 below, where four waves share a SIMD), or the copies wait; the
-// longer it is, the fewer records are still in the caches.  Compression alone,
-// at 8 / 9 / 10 / 12 rows: cosmology 64M x 6 489 / 503 / 509 / 512 us, LiDAR
-// 20M x 3 131 / 123 / 127 / 128; B = 512, 4M x 6 83 / 73 / 71 / 68.  With 2 or
-// 8 parts 525 and 510 (64M, 12 rows, 4 parts 512).
+// B = 1024, 8 below, where four waves share a SIMD) and what they take to
+// finish, or the copies wait; the longer it is, the fewer records are still in
+// the caches, and the more are left to the copy kernel.  Whole calls in us
+// without copies, then at delays of 6 / 7 / 8 / 9 / 10 / 12 rows: cosmology 64M x 6
+// 594, 747 / 528 / 518 / 523 / 527 / 539; LiDAR 20M x 3 with its range pass 217,
+// 233 / 206 / 201 / 200 / 201 / 201; md 8M x 6 both ways 172, 194 / 171 / 167 /
+// 167 / 167 / 168; float64 12.6M x 3 164, 204 / 167 / 158 / 157 / 157 / 157; B = 512,
+// 10.5M x 6 161, 303 / 252 at 7, 151 / 142 / 141 at 9, 10, 12; B = 256, 5.2M x 6
+// 124, 187 at 7, 119 / 110 / 105 at 9, 10, 12.  With 2 or 8 parts instead of 4,
+// at 12 rows: 525 and 510 us for the compression of 64M x 6, 512 with 4.
+// Not at B = 2048: its encoder takes four times as long a particle as the
+// copies, which change it by -1.5 to +2.6 % (6.3M to 42M particles).
 constexpr uint32_t kXcds = 8;
 constexpr uint32_t kPlaceParts = 4;
-__host__ __device__ inline uint32_t place_delay(uint32_t B) { return B >= 1024 ? 8u : 12u; }
+__host__ __device__ inline uint32_t place_delay(uint32_t B) { return B == 1024 ? 8u : 12u; }
 __host__ __device__ inline uint64_t placed_rows(uint64_t nb) {
     return (nsuper_of(nb) + kXcds - 1) / kXcds;
 }

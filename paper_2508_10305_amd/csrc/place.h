@@ -28,7 +28,7 @@
 // it.  Every wait is bounded: a copying wave that has waited kPlaceSpins times,
 // or meets a block left to the generic encoder, leaves its records to the copy
 // kernel, so no result depends on the order in which the hardware starts
-// workgroups, and no wave waits for one that may not have started.
+// workgroups, and a wave that waits for one that has not started goes on.
 #pragma once
 
 #include "gpz_internal.h"

@@ -1,5 +1,5 @@
 """Record copies inside the encoder's launch at every block size that has them
-and in float64: streams equal the oracle's, also from a workspace off the
+(B = 2048 has none, at the same sizes) and in float64: streams equal the oracle's, also from a workspace off the
 alignment the copies ask for, and the copies do happen: the encoder's flags in
 the workspace say which parts of a superblock it copied (all others are left to
 the copy kernel, so the stream alone would not show a launch that copies
@@ -79,10 +79,11 @@ def test_every_block_size(gpz, orc, B, rows):
     got, flags = compress(gpz, host, 1e-3, B)
     assert got.size == ref.size and (got == ref).all()
     placed = (rows - delay(B)) * XCDS
-    # (waits are bounded, so not every part need be copied; a launch that
-    # copies less than half has lost what it is for)
-    assert parts(flags[:placed]).sum() > placed * PARTS // 2
-    assert (flags[placed:] == 0).all()
+    if B <= 1024:
+        # (waits are bounded, so not every part need be copied; a launch that
+        # copies less than half has lost what it is for)
+        assert parts(flags[:placed]).sum() > placed * PARTS // 2
+        assert (flags[placed:] == 0).all()
     got, _ = compress(gpz, host, 1e-3, B, shift=16)
     assert got.size == ref.size and (got == ref).all()
 
