@@ -410,13 +410,16 @@ def main():
 
     # algorithmic bytes per launch: what each kernel must read and write.  The
     # encoder reads the snapshot and writes the records (C minus the stream's
-    # tables) to their slots.  The copy's bytes (the records once more) are not
-    # counted: of a large snapshot the encoder's launch moves most of them, of a
-    # small one the copy kernel all.
+    # tables) to their slots; the copy reads and writes them once more.  Of a
+    # large snapshot the encoder's launch copies all but the last rows (of one
+    # superblock per XCD) beside that, which is not counted there, and the copy
+    # kernel is left with those rows.
     rec = C - 4 * (8 + 2 * ((nb + 63) // 64) + F + nb)
     nsup = (nb + 63) // 64
+    rows, last = (nsup + 7) // 8, 8  # (the library's rule at its default block size)
+    copied = rec * last // rows if rows >= last + 4 else rec
     algo = {"encode": S + rec, "decode": C + S, "prepare": 4 * (2 * nb + 7 + nsup),
-            "scan": 12 * nsup, "copy": 0, "generic": 0}
+            "scan": 12 * nsup, "copy": 2 * copied, "generic": 0}
     dominant = max(avg, key=lambda k: avg[k])
     ach = algo[dominant] / (avg[dominant] * 1e-3) / 1e9
     traffic = None
