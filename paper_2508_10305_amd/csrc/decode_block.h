@@ -83,8 +83,8 @@ __device__ __forceinline__ void post_header(const DecodeArgs& a) {
 }
 
 // The stream as constant memory: no kernel writes it, and said so, a word at the
-// same index for all lanes stays a scalar load also after a store (without, every
-// word read after the one that reports a foreign header was a vector load).
+// same index for all lanes stays a scalar load (without, every one after the
+// store that reports a bad record was a vector load).
 typedef const uint32_t __attribute__((address_space(4))) StreamWord;
 __device__ __forceinline__ const StreamWord* stream_words(const uint32_t* p) {
     return (const StreamWord*)(uintptr_t)p;
@@ -111,14 +111,16 @@ __device__ __forceinline__ bool eb_table_bad(const DecodeArgs& a, uint32_t lane)
 }
 
 // The record of block b: false (and *a.err set) when the stream's header,
-// tables or lengths are not those of the stream asked for.  The header comes
-// first: a synchronous call starts with the decoder for the default parameters,
-// and on any other stream its blocks end there, after one round trip (block 0
-// reports it; 128M particles at B = 512: the whole call 306 us when every block
-// went through the tables and stored the flag, 286 now, 288 with the header
-// fetched before any decoder runs).  The superblock
-// entry is checked against the record area before anything is added to it,
-// and the lengths are summed in 64 bits, so no sum can wrap and every
+// tables or lengths are not those of the stream asked for.  A foreign header is
+// reported by block 0 alone: a synchronous call starts with the decoder for the
+// default parameters, whose every block finds one on any other stream, and the
+// flag is then in host memory.  Its words are scalar loads beside the
+// tables' and cost no round trip of their own (128M particles at B = 512: the
+// whole call 306 us when the header came last and every block stored the flag,
+// 287 now, 288 with the header fetched before any decoder runs; 285 when a
+// block ended at the header, which cost every other stream 0.1 us).  The
+// superblock entry is checked against the record area before anything is added
+// to it, and the lengths are summed in 64 bits, so no sum can wrap and every
 // accepted [rec, rec + len) lies inside the record area.
 __device__ __forceinline__ bool locate_record(const DecodeArgs& a, uint32_t b, uint32_t lane,
                                               uint32_t types, const uint32_t*& rec,
@@ -132,10 +134,6 @@ __device__ __forceinline__ bool locate_record(const DecodeArgs& a, uint32_t b, u
     const uint64_t sup_off = (uint64_t)sup[2 * sb] | ((uint64_t)sup[2 * sb + 1] << 32);
     const bool other = other_stream(a, types);
     const uint64_t mine = (first + lane < b) ? (uint64_t)lens[first + lane] : 0ull;
-    if (other) {
-        if (b == 0 && lane == 0) *a.err = 1u;
-        return false;
-    }
     const uint64_t sum = sup_off + wave_sum_u64(mine);
     // every lane holds the same sum: taken from lane 0 it is a scalar, and so
     // are the record pointer and every header word read through it
@@ -152,8 +150,8 @@ __device__ __forceinline__ bool locate_record(const DecodeArgs& a, uint32_t b, u
         const uint64_t prev = ((uint64_t)sup[2 * sb - 2] | ((uint64_t)sup[2 * sb - 1] << 32));
         if (prev > rec_total || prev + wave_sum_u64(pl) != off) bad = true;
     }
-    if (__any(bad)) {
-        if (lane == 0) *a.err = 1u;
+    if (other || __any(bad)) {
+        if (lane == 0 && (b == 0 || !other)) *a.err = 1u;
         return false;
     }
     rec = a.in + a.prefix + off;
