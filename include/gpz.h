@@ -94,6 +94,9 @@ uint64_t gpz_max_compressed_bytes(uint64_t n, uint32_t nfields, const gpz_params
  * bytes.  Returns 0 for invalid parameters. */
 uint64_t gpz_compress_workspace_bytes(uint64_t n, uint32_t nfields, const gpz_params *p);
 
+/* Alignment.  A stream is a sequence of 32-bit words: stream buffers are 4-byte
+ * aligned, fields and permutations aligned to their elements. */
+
 /* Memory of the synchronous calls (gpz_compress, gpz_decompress, their float64
  * forms and the reporting calls; the _async and _noalloc calls use none of
  * this).  Given a workspace they allocate no device memory.  Each borrows, until

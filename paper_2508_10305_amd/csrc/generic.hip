@@ -671,7 +671,7 @@ hipError_t launch_encode_deferred_then_scan(const EncodeArgs& a, const ScanArgs&
     const uint32_t g = 2u * device_cu_count();
     const dim3 grid(a.nblocks < g ? (a.nblocks ? a.nblocks : 1u) : g), block(kT);
     // (the wave-per-block encoder's blocks hold at most 2048 particles: with the
-    // 57 KB of LDS of 4096 an empty walk took 30 us, with the 29 KB of 2048 7 us)
+    // 57 KB of LDS of 4096 an empty walk took 30 us, with the 30 KB of 2048 7 us)
     if (a.B <= 1024)
         hipLaunchKernelGGL(gen_encode_deferred_then_scan<1024>, grid, block, 0, s, a, sa, done);
     else
