@@ -45,8 +45,8 @@ __host__ __device__ inline uint32_t bit_width(uint32_t v) { return v ? 32u - (ui
 // 10.5M x 6 161, 303 / 252 at 7, 151 / 142 / 141 at 9, 10, 12; B = 256, 5.2M x 6
 // 124, 187 at 7, 119 / 110 / 105 at 9, 10, 12.  With 2 or 8 parts instead of 4,
 // at 12 rows: 525 and 510 us for the compression of 64M x 6, 512 with 4.
-// Not at B = 2048: its encoder takes four times as long a particle as the
-// copies, which change it by -1.5 to +2.6 % (6.3M to 42M particles).
+// Not at B = 2048, where copies in the launch change a call by -1.5 to +2.6 %
+// (2 and 6 fields, 12.6M to 42M particles).
 constexpr uint32_t kXcds = 8;
 constexpr uint32_t kPlaceParts = 4;
 __host__ __device__ inline uint32_t place_delay(uint32_t B) { return B == 1024 ? 8u : 12u; }
